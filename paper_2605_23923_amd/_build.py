@@ -6,6 +6,8 @@ import os
 import re
 import shutil
 import subprocess
+import tempfile
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
@@ -13,14 +15,14 @@ LIB = os.path.join(HERE, "libsu2fft.so")
 # per-kernel register, scratch and occupancy figures the compiler reported for
 # the library last built (a build product, next to the library)
 RESOURCES = os.path.join(HERE, "kernel_resources.json")
-# su2fft_kernels.hip is the one translation unit of the transform kernels: it
-# includes su2fft_ring.hip, su2fft_ring_fast.hip, su2fft_beta.hip and
-# su2fft_beta_bf16.hip and adds the work-list kernels of mixed plans
-SOURCES = ["su2fft_host.hip", "su2fft_kernels.hip", "su2fft_table.hip", "su2fft_calib.hip"]
+# su2fft_kernels.hip includes su2fft_ring_fast.hip, su2fft_beta.hip,
+# su2fft_beta_bf16.hip and the other kernels that mixed plans' work lists run
+# too; the sources below are compiled side by side and linked
+SOURCES = ["su2fft_kernels.hip", "su2fft_ring_radix.hip", "su2fft_host.hip", "su2fft_table.hip", "su2fft_calib.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 FLAGS = [
-    "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
+    "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     # packed FP32 instructions stay off: the compiler must not form v_pk_* FP32 ops
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wno-unused-result",
@@ -60,16 +62,24 @@ def parse_resource_report(text: str) -> dict:
 
 
 def build(verbose: bool = False) -> str:
-    tmp = LIB + ".tmp"
-    cmd = [HIPCC, *FLAGS, "-o", tmp, *[os.path.join(CSRC, s) for s in SOURCES]]
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    res = subprocess.run(cmd, capture_output=True, text=True)
-    if res.returncode != 0:
-        raise RuntimeError("hipcc failed:\n" + res.stdout + res.stderr)
-    os.replace(tmp, LIB)
+    with tempfile.TemporaryDirectory() as tmp:
+        objs = [os.path.join(tmp, s + ".o") for s in SOURCES]
+        cmds = [[HIPCC, *FLAGS, "-c", os.path.join(CSRC, s), "-o", o] for s, o in zip(SOURCES, objs)]
+        if verbose:
+            for cmd in cmds:
+                print(" ".join(cmd), flush=True)
+        with ThreadPoolExecutor(len(cmds)) as pool:
+            res = list(pool.map(lambda c: subprocess.run(c, capture_output=True, text=True), cmds))
+        for r in res:
+            if r.returncode != 0:
+                raise RuntimeError("hipcc failed:\n" + r.stdout + r.stderr)
+        link = subprocess.run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", LIB + ".tmp"],
+                              capture_output=True, text=True)
+        if link.returncode != 0:
+            raise RuntimeError("hipcc failed:\n" + link.stdout + link.stderr)
+    os.replace(LIB + ".tmp", LIB)
     with open(RESOURCES, "w") as fh:
-        json.dump(parse_resource_report(res.stderr), fh, indent=1, sort_keys=True)
+        json.dump(parse_resource_report("".join(r.stderr for r in res)), fh, indent=1, sort_keys=True)
     return LIB
 
 

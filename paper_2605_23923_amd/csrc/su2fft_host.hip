@@ -21,7 +21,9 @@ static thread_local int32_t g_last_hip_error = 0;
 // the array's name only stands for the symbol; host code uses the device
 // address hipGetSymbolAddress returns on each GPU (scratch_address), never
 // the name itself.
-static __device__ __align__(256) unsigned char scratch[SU2_NOALLOC_SCRATCH_BYTES];
+// A sixteenth more than the documented limit: the point-symmetric pair list of
+// the mixed-radix plans holds up to that many pads beyond P16.
+static __device__ __align__(256) unsigned char scratch[SU2_NOALLOC_SCRATCH_BYTES / 16 * 17];
 constexpr int SCRATCH_MAX_DEVICES = 64;
 static std::mutex g_scratch_mu;
 static void* g_scratch_addr[SCRATCH_MAX_DEVICES] = {};
@@ -63,36 +65,9 @@ bool only_2_3(int n) {
   return n == 1;
 }
 
-// radix sequence for a length that is a product of 2s and 3s: 8s first, then
-// a 4 or a 2 for the rest of the power of two, then 3s.
 }  // namespace su2
 
 namespace {
-
-int radix_plan(int L, int* rad) {
-  int n = 0;
-  int p2 = 0, p3 = 0;
-  while (L % 2 == 0) { L /= 2; p2++; }
-  while (L % 3 == 0) { L /= 3; p3++; }
-  while (p2 >= 3) { rad[n++] = 8; p2 -= 3; }
-  if (p2 == 2) rad[n++] = 4;
-  if (p2 == 1) rad[n++] = 2;
-  for (int i = 0; i < p3; i++) rad[n++] = 3;
-  return n;
-}
-
-// position of frequency q after in-place decimation-in-frequency passes with
-// the given radix sequence on a length-L line
-int dif_position(int q, int L, const int* rad, int nrad) {
-  int pos = 0;
-  for (int s = 0; s < nrad; s++) {
-    const int R = rad[s];
-    L /= R;
-    pos += (q % R) * L;
-    q /= R;
-  }
-  return pos;
-}
 
 int imod(int a, int n) { return ((a % n) + n) % n; }
 
@@ -138,24 +113,17 @@ namespace {
 
 template <class T>
 hipError_t upload_typed(su2_plan_s* pl, const std::vector<long double>& W, const std::vector<long double>& twr,
-                        const std::vector<long double>& twi, const std::vector<int>& rho_e) {
+                        const std::vector<long double>& twi) {
   const int N = pl->N;
   std::vector<T> hW(N);
   for (int i = 0; i < N; i++) hW[i] = (T)W[i];
   std::vector<cpx<T>> htw(2 * N);
   for (int i = 0; i < 2 * N; i++) htw[i] = {(T)twr[i], (T)twi[i]};
-  std::vector<cpx<T>> hrho(pl->P_pad);
-  const T ir[4] = {1, 0, -1, 0}, ii[4] = {0, 1, 0, -1};  // i^e
-  for (int p = 0; p < pl->P_pad; p++) hrho[p] = {ir[rho_e[p]], ii[rho_e[p]]};
   hipError_t e;
   if ((e = pl->alloc(&pl->d_W, sizeof(T) * N)) != hipSuccess) return e;
   if ((e = pl->alloc(&pl->d_tw, sizeof(cpx<T>) * 2 * N)) != hipSuccess) return e;
-  if ((e = pl->alloc(&pl->d_rho, sizeof(cpx<T>) * pl->P_pad)) != hipSuccess) return e;
   if ((e = hipMemcpy(pl->d_W, hW.data(), sizeof(T) * N, hipMemcpyHostToDevice)) != hipSuccess) return e;
-  if ((e = hipMemcpy(pl->d_tw, htw.data(), sizeof(cpx<T>) * 2 * N, hipMemcpyHostToDevice)) != hipSuccess) return e;
-  if ((e = hipMemcpy(pl->d_rho, hrho.data(), sizeof(cpx<T>) * pl->P_pad, hipMemcpyHostToDevice)) != hipSuccess)
-    return e;
-  return hipSuccess;
+  return hipMemcpy(pl->d_tw, htw.data(), sizeof(cpx<T>) * 2 * N, hipMemcpyHostToDevice);
 }
 
 }  // namespace
@@ -209,6 +177,37 @@ hipError_t upload_otf_scalars(su2_plan_s* pl, const std::vector<long double>& be
   return hipMemcpy(pl->d_nodes, nodes.data(), sizeof(double) * nodes.size(), hipMemcpyHostToDevice);
 }
 
+// The pair runs of every column of the bin map (RadixRingParams::cols); false
+// if the pairs or phases of a column do not follow one (every bin is checked).
+static bool radix_columns(int N, const std::vector<int>& bins, std::vector<int>& cols) {
+  cols.assign((size_t)4 * N, 0);
+  for (int q = 0; q < N; q++) {
+    const int* bq = &bins[(size_t)q * N];
+    int* cq = &cols[(size_t)4 * q];
+    int nneg = 0, npos = 0;
+    while (npos < N / 2 && bq[npos] >= 0) npos++;
+    while (nneg < N / 2 && bq[N - 1 - nneg] >= 0) nneg++;
+    if (nneg > 127 || npos > 127 || (nneg > 0 && npos == 0)) return false;
+    if (npos > 0) {
+      const int e0 = bq[0] & 3;
+      cq[0] = nneg > 0 ? (bq[N - 1] >> 2) + 1 : 0;
+      cq[1] = bq[0] >> 2;
+      cq[2] = npos > 1 ? (bq[1] >> 2) - 1 : 0;
+      cq[3] = e0 | (nneg << 2) | (npos << 9);
+    }
+    for (int p = 0; p < N; p++) {
+      const int ps = p < N / 2 ? p : p - N;
+      if (ps < -nneg || ps >= npos) {
+        if (bq[p] >= 0) return false;
+        continue;
+      }
+      const int pair = ps < 0 ? cq[0] + ps : (ps == 0 ? cq[1] : cq[2] + ps);
+      if (bq[p] != ((pair << 2) | (((cq[3] & 3) + 3 * ps) & 3))) return false;
+    }
+  }
+  return true;
+}
+
 su2_status_t build_plan(su2_plan_s* pl) {
   const int B = pl->B, N = 2 * B;
   const bool so3 = pl->so3;
@@ -241,70 +240,42 @@ su2_status_t build_plan(su2_plan_s* pl) {
     void* scr = nullptr;
     if ((e = scratch_address(dev, &scr)) != hipSuccess) return hip_fail(e);
   }
-  int max_lds = 0;
-  if ((e = hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev)) != hipSuccess)
-    return hip_fail(e);
-
-  // gamma-frequency classes: the smallest divisor of N whose class fits in LDS
-  int split = 0;
-  for (int s = 1; s <= MAX_SPLIT; s++) {
-    if (N % s) continue;
-    const size_t need = ((size_t)N * (N / s) + 2 * (size_t)N) * cb;
-    if (need <= (size_t)max_lds) { split = s; break; }
-  }
-  if (split == 0) return SU2_ERR_UNSUPPORTED;
-  // the register-resident ring kernels handle the whole ring themselves and
-  // want the pairs ordered by 2m alone
   pl->fast = (pl->dtype == SU2_C128) ? fast_ring_supported<double>(N) : fast_ring_supported<float>(N);
   const bool n256 = !pl->fast && large_ring_supported(N);
   pl->sliced = n256 && pl->dtype != SU2_C128;
   pl->large = n256;
   // only the register-resident rings have a half-spectrum form for real signals
   pl->real_io = pl->real && !pl->fast;
-  if (pl->fast || n256) split = 1;
-  pl->split = split;
-  pl->Nc = N / split;
-  pl->nrad_c = radix_plan(pl->Nc, pl->rad_c);
-  pl->nrad_n = radix_plan(N, pl->rad_n);
 
-  // pairs (m, n): grouped by class r = (2m mod N) mod split, then 2m, then 2n
+  // pairs (m, n) ordered by 2m, then 2n
   std::vector<PairInfo> pairs;
-  std::vector<int> fftpos, rho_e;
+  std::vector<int> rho_e;
   long long tab = 0;
-  for (int r = 0; r < split; r++) {
-    pl->cls_begin[r] = (int)pairs.size();
-    for (int tm = -(B - 1); tm <= B - 1; tm++) {
-      if (so3 && (tm & 1)) continue;  // SO(3): integer m only
-      const int q = bin_q(tm);
-      if (q % split != r) continue;
-      const int qp = q / split;
-      const int ccol = dif_position(qp, pl->Nc, pl->rad_c, pl->nrad_c);
-      for (int tn = -(B - 1); tn <= B - 1; tn++) {
-        if ((tn - tm) & 1) continue;
-        if (so3 && (tn & 1)) continue;
-        PairInfo pi;
-        pi.tm = tm; pi.tn = tn;
-        pi.tl0 = abs(tm) > abs(tn) ? abs(tm) : abs(tn);
-        pi.L = (B - 1 - pi.tl0) / 2 + 1;
-        pi.tab = 0;
-        pi.lsum = 0;
-        pi.coff = 0;
-        pi.itab = 0;
-        pairs.push_back(pi);
-        const int palpha = bin_p(tn);
-        const int jrow = dif_position(palpha, N, pl->rad_n, pl->nrad_n);
-        fftpos.push_back(jrow * pl->Nc + ccol);
-        rho_e.push_back(phase_e(tm, tn));
-      }
+  for (int tm = -(B - 1); tm <= B - 1; tm++) {
+    if (so3 && (tm & 1)) continue;  // SO(3): integer m only
+    for (int tn = -(B - 1); tn <= B - 1; tn++) {
+      if ((tn - tm) & 1) continue;
+      if (so3 && (tn & 1)) continue;
+      PairInfo pi;
+      pi.tm = tm; pi.tn = tn;
+      pi.tl0 = abs(tm) > abs(tn) ? abs(tm) : abs(tn);
+      pi.L = (B - 1 - pi.tl0) / 2 + 1;
+      pi.tab = 0;
+      pi.lsum = 0;
+      pi.coff = 0;
+      pi.itab = 0;
+      pairs.push_back(pi);
+      rho_e.push_back(phase_e(tm, tn));
     }
-    pl->cls_end[r] = (int)pairs.size();
   }
   pl->P = (int)pairs.size();
-  // Layout of the pair list.  Point-symmetric where the ring kernels take the
-  // pairs in one class ordered by (2m, 2n) (the list is then centrally
-  // symmetric: its mirror (-m, -n) of position i sits at P - 1 - i), the plan
-  // keeps a table (the on-the-fly plans keep none) and the padding fits the
-  // ring kernels' slices: the pairs with 2m < 0, padded to whole tiles; the
+  // Layout of the pair list.  Ordered by (2m, 2n) it is centrally symmetric
+  // (the mirror (-m, -n) of position i sits at P - 1 - i).  Padded to keep
+  // that symmetry tile by tile where the plan keeps a table (the on-the-fly
+  // plans keep none) and the padding fits the register-resident kernels'
+  // slices or, for the mixed-radix rings, costs at most one tile in 16 (from
+  // B = 18 up: below, the table is a few KB and the added tiles cost more
+  // than its second half): the pairs with 2m < 0, padded to whole tiles; the
   // 2m = 0 run with one pad right after (0, 0) and as many pads on both ends
   // as whole tiles need; the pads of the first part again; the pairs with
   // 2m > 0.  Position i then mirrors position P_pad - 1 - i, tile t mirrors
@@ -318,7 +289,7 @@ su2_status_t build_plan(su2_plan_s* pl) {
     return pi;
   };
   std::vector<int> order;  // index into `pairs` per position, -1 for a pad
-  bool sym = split == 1 && !pl->otf && (pl->fast || n256);  // not the generic ring kernel (class ranges)
+  bool sym = !pl->otf;
   if (sym) {
     int nA = 0, R0 = 0;
     for (const PairInfo& q : pairs) { nA += q.tm < 0; R0 += q.tm == 0; }
@@ -345,6 +316,7 @@ su2_status_t build_plan(su2_plan_s* pl) {
       }
     }
     if (T % PT) sym = false;
+    if (!pl->fast && !n256 && 16 * T > 17 * ((pl->P + PT - 1) / PT * PT)) sym = false;
     // the slices of the register-resident ring kernels must still fit
     if (sym && pl->fast) {
       const int cap = pl->dtype == SU2_C128 ? fast_ring_slice_capacity<double>(N) : fast_ring_slice_capacity<float>(N);
@@ -368,23 +340,20 @@ su2_status_t build_plan(su2_plan_s* pl) {
   pl->sym = sym;
   {
     std::vector<PairInfo> np;
-    std::vector<int> nf, nr;
+    std::vector<int> nr;
     for (int o : order) {
       if (o < 0) {
         np.push_back(pad_pair());
-        nf.push_back(0);
         nr.push_back(0);
       } else {
         PairInfo q = pairs[o];
         q.tsign = 1;
         q.towner = 1;
         np.push_back(q);
-        nf.push_back(fftpos[o]);
         nr.push_back(rho_e[o]);
       }
     }
     pairs.swap(np);
-    fftpos.swap(nf);
     rho_e.swap(nr);
   }
   pl->P_pad = (int)pairs.size();
@@ -459,11 +428,14 @@ su2_status_t build_plan(su2_plan_s* pl) {
     const int cap = pl->dtype == SU2_C128 ? fast_ring_slice_capacity<double>(N) : fast_ring_slice_capacity<float>(N);
     if (pl->fast && pl->rend[r] - pl->rbeg[r] > cap) return SU2_ERR_UNSUPPORTED;
   }
+  // mixed-radix rings: per gamma frequency q the pair runs of its bins
+  // (RadixRingParams::cols), checked against the bin map
+  std::vector<int> cols;
+  if (!pl->fast && !n256 && !radix_columns(N, bins, cols)) return SU2_ERR_UNSUPPORTED;
   // one-pass N = 256 kernels (FP32): per gamma frequency q the bases from
   // which the kernels compute every bin's pair and phase (FastRingParams::cols),
   // checked here against the bin map; if the pair layout does not follow them,
   // the plan keeps the two-pass kernels
-  std::vector<int> cols;
   if (pl->sliced) {
     cols.assign((size_t)4 * N, 0);
     bool ok = true;
@@ -510,8 +482,6 @@ su2_status_t build_plan(su2_plan_s* pl) {
       if (qrange[2 * blk + 1] - qrange[2 * blk] > large_ring_slice_capacity()) return SU2_ERR_UNSUPPORTED;
     }
   }
-  std::vector<int> colq(pl->Nc);
-  for (int qp = 0; qp < pl->Nc; qp++) colq[dif_position(qp, pl->Nc, pl->rad_c, pl->nrad_c)] = qp;
 
   std::vector<long double> alpha, beta, gamma, W;
   grid_ld(B, alpha, beta, gamma, W, so3);
@@ -524,8 +494,6 @@ su2_status_t build_plan(su2_plan_s* pl) {
   // device tables
   double* d_beta = nullptr;
   if ((e = pl->alloc((void**)&pl->d_pairs, sizeof(PairInfo) * pl->P_pad)) != hipSuccess) return hip_fail(e);
-  if ((e = pl->alloc((void**)&pl->d_fftpos, sizeof(int) * pl->P_pad)) != hipSuccess) return hip_fail(e);
-  if ((e = pl->alloc((void**)&pl->d_colq, sizeof(int) * pl->Nc)) != hipSuccess) return hip_fail(e);
   if ((e = pl->alloc((void**)&d_beta, sizeof(double) * N)) != hipSuccess) return hip_fail(e);
   // the bin maps in the register-resident kernels' reading order: the
   // entries of (q, p2) for the kept rows p1 of the alpha split, contiguous
@@ -560,16 +528,12 @@ su2_status_t build_plan(su2_plan_s* pl) {
   }
   if ((e = hipMemcpy(pl->d_pairs, pairs.data(), sizeof(PairInfo) * pl->P_pad, hipMemcpyHostToDevice)) != hipSuccess)
     return hip_fail(e);
-  if ((e = hipMemcpy(pl->d_fftpos, fftpos.data(), sizeof(int) * pl->P_pad, hipMemcpyHostToDevice)) != hipSuccess)
-    return hip_fail(e);
-  if ((e = hipMemcpy(pl->d_colq, colq.data(), sizeof(int) * pl->Nc, hipMemcpyHostToDevice)) != hipSuccess)
-    return hip_fail(e);
   if ((e = hipMemcpy(d_beta, hbeta.data(), sizeof(double) * N, hipMemcpyHostToDevice)) != hipSuccess)
     return hip_fail(e);
   if (pl->dtype == SU2_C128)
-    e = upload_typed<double>(pl, W, twr, twi, rho_e);
+    e = upload_typed<double>(pl, W, twr, twi);
   else
-    e = upload_typed<float>(pl, W, twr, twi, rho_e);
+    e = upload_typed<float>(pl, W, twr, twi);
   if (e != hipSuccess) return hip_fail(e);
 
   // per-pair and per-node recurrence scalars: the on-the-fly tables and the
@@ -654,7 +618,7 @@ su2_status_t run_stage_t(su2_plan_s* pl, su2_stage_t stage, const void* in, void
       else if (pl->fast)
         e = launch_ring_forward_fast<T>(fast_params<T>(pl, 0), (const cpx<T>*)in, (cpx<T>*)S, s);
       else
-        e = launch_ring_forward<T>(ring_params<T>(pl, 0), (const cpx<T>*)in, (cpx<T>*)S, s);
+        e = launch_ring_forward_radix<T>(radix_params<T>(pl, 0), (const cpx<T>*)in, (cpx<T>*)S, s);
       break;
     case SU2_STAGE_BETA_FORWARD:
       if (pl->otf)
@@ -689,8 +653,8 @@ su2_status_t run_stage_t(su2_plan_s* pl, su2_stage_t stage, const void* in, void
         e = launch_ring_inverse_fast<T>(fast_params<T>(pl, stage == SU2_STAGE_RING_ADJOINT), (const cpx<T>*)S,
                                         (cpx<T>*)out, s);
       else
-        e = launch_ring_inverse<T>(ring_params<T>(pl, stage == SU2_STAGE_RING_ADJOINT), (const cpx<T>*)S,
-                                   (cpx<T>*)out, s);
+        e = launch_ring_inverse_radix<T>(radix_params<T>(pl, stage == SU2_STAGE_RING_ADJOINT), (const cpx<T>*)S,
+                                         (cpx<T>*)out, s);
       break;
     default:
       return SU2_ERR_INVALID_VALUE;
@@ -902,7 +866,10 @@ su2_status_t su2_forward_noalloc(su2_plan_t plan, const void* d_samples, void* d
   if (!plan || !d_samples || !d_coeffs || plan->mixed) return SU2_ERR_INVALID_VALUE;
   // the two-pass forward ring (N = 256 in FP64) keeps a second plan-owned buffer
   if (plan->large && !plan->sliced) return SU2_ERR_UNSUPPORTED;
-  const size_t need = (plan->dtype == SU2_C128 ? 16 : 8) * (size_t)plan->P_pad * plan->N * plan->batch;
+  // the documented limit counts the pairs rounded up to 16; the scratch has
+  // room for the mixed-radix plans' symmetric padding beyond that
+  const size_t pairs = plan->fast || plan->large ? plan->P_pad : (plan->P + PT - 1) / PT * PT;
+  const size_t need = (plan->dtype == SU2_C128 ? 16 : 8) * pairs * plan->N * plan->batch;
   if (need > SU2_NOALLOC_SCRATCH_BYTES) return SU2_ERR_UNSUPPORTED;
   int dev = -1;
   hipError_t e = hipGetDevice(&dev);

@@ -16,10 +16,6 @@ namespace su2 {
 // so that a ring (b, k) writes PT contiguous values per tile and a beta
 // contraction over one tile reads, for each k, a contiguous [b][PT] slab.
 constexpr int PT = 16;
-constexpr int MAX_RADICES = 8;
-constexpr int MAX_SPLIT = 8;
-constexpr int FFT_THREADS = 256;
-constexpr int GEMM_THREADS = 256;
 
 template <class T>
 struct cpx {
@@ -76,23 +72,17 @@ __host__ __device__ inline long long inverse_table_elems(int L, int N) {
   return (long long)((L + 3) / 4) * ((N + 15) / 16) * 64;
 }
 
-// Parameters of the ring-FFT kernels (one workgroup per ring (signal, k)).
+// Parameters of the mixed-radix ring kernels (su2fft_ring_radix.hip).
 template <class T>
-struct RingParams {
-  int N;          // nodes per angle
-  int Nc;         // columns held in LDS at once: N / split
-  int split;      // number of gamma-frequency classes processed one after another
-  int batch;
-  int ntiles;     // pair tiles
-  int nrad_c, nrad_n;
-  int rad_c[MAX_RADICES];   // radix sequence of the length-Nc gamma transform
-  int rad_n[MAX_RADICES];   // radix sequence of the length-N alpha transform
-  int cls_begin[MAX_SPLIT], cls_end[MAX_SPLIT];  // pair ranges per class
+struct RadixRingParams {
+  int N, batch;
   const cpx<T>* tw;         // e^{+i pi t / N}, t = 0..2N-1
   const T* W;               // beta weights W_k
-  const int* fftpos;        // per pair: LDS position (row * Nc + column) of its bin
-  const cpx<T>* rho;        // per pair: phase i^{n-m} (-1)^{2m} e^{-i pi n}
-  const int* colq;          // per LDS column c': q' with pos(q') = c'
+  // per gamma frequency q: the pair index of bin p = ps mod N is x + ps for
+  // ps < 0, y for ps = 0, z + ps for ps > 0 (x, y, z, w of the entry); ps runs
+  // over [-nneg, npos), the phase exponent is (e0 + 3 ps) mod 4, and
+  // w = e0 | nneg << 2 | npos << 9
+  const int4* cols;
   int adjoint;              // inverse chain: 0 -> plain, 1 -> multiply by W_k
   const long long* soff;    // per signal: offset of its samples (complex values), or null: b * N^3
   int so3;                  // SO(3) plan: integer n only, no half-bin shift on any q
@@ -147,10 +137,19 @@ struct FastRingParams {
 // zero imaginary part (a known zero would be folded away and change which
 // products become FMAs, and with them the rounding).
 template <class T>
-__device__ __forceinline__ T opaque_zero() {
+__host__ __device__ __forceinline__ T opaque_zero() {
   T z = T(0);
+#ifdef __HIP_DEVICE_COMPILE__
   asm volatile("" : "+v"(z));
+#endif
   return z;
+}
+// a use of v that the compiler cannot drop
+template <class T>
+__host__ __device__ __forceinline__ void keep_value(T v) {
+#ifdef __HIP_DEVICE_COMPILE__
+  asm volatile("" ::"v"(v));
+#endif
 }
 template <class T>
 __device__ __forceinline__ cpx<T> ld_sample(const cpx<T>* base, size_t idx, int real_io) {
@@ -293,9 +292,9 @@ struct bf16x2_t {
 
 // ---- kernel launchers (defined in the .hip files) ----
 template <class T>
-hipError_t launch_ring_forward(const RingParams<T>& p, const cpx<T>* samples, cpx<T>* S, hipStream_t s);
+hipError_t launch_ring_forward_radix(const RadixRingParams<T>& p, const cpx<T>* samples, cpx<T>* S, hipStream_t s);
 template <class T>
-hipError_t launch_ring_inverse(const RingParams<T>& p, const cpx<T>* S, cpx<T>* samples, hipStream_t s);
+hipError_t launch_ring_inverse_radix(const RadixRingParams<T>& p, const cpx<T>* S, cpx<T>* samples, hipStream_t s);
 template <class T>
 hipError_t launch_beta_forward(const BetaParams<T>& p, const cpx<T>* S, cpx<T>* coeffs, hipStream_t s);
 template <class T>

@@ -5,11 +5,11 @@
 // and the ring-spectrum workspace of a single-B plan; its signals stay where
 // the caller put them (concatenated in order), reached through per-signal
 // offset tables.  A transform runs as work lists: one of (group, signal,
-// node) ring tasks per ring kernel family, and the (group, pair tile, signal
+// node) ring tasks of the register-resident kernels, and the (group, pair tile, signal
 // tile) contraction tasks split by contraction shape class and tile width, each launch
 // calling the same kernel bodies as the single-B launches (so every signal's
-// result is bit-identical to a single-B plan's); the rings of N = 256 groups
-// run the single-B plan's own N = 256 kernels beside the work lists.  Tasks
+// result is bit-identical to a single-B plan's); the rings of mixed-radix and
+// N = 256 groups run the single-B plan's own kernels beside the work lists.  Tasks
 // are ordered by decreasing cost and taken in a static stride by a grid of
 // `knob x CUs` workgroups, or (knob 0) one workgroup per task; the knob of
 // each kernel is chosen by timing the candidates at plan creation
@@ -29,7 +29,6 @@
 #include <string>
 #include <vector>
 
-#include "su2fft_ring.hip"
 #include "su2fft_ring_fast.hip"
 #include "su2fft_ring_large.hip"
 #include "su2fft_ring_sliced.hip"
@@ -51,7 +50,6 @@ struct GroupDev {
   int fast;               // register-resident ring kernels
   int rtmax, lq, lq2;     // contraction shapes of the group's bandlimit
   int narrow_f, narrow_i; // 16-signal contraction tiles (forward, inverse) instead of the widest
-  RingParams<T> rp[3];    // generic ring kernels: forward, inverse, adjoint
   FastRingParams<T> fp[3];
   BetaParams<T> bp[3];    // contraction: forward, inverse, adjoint
   const unsigned* tabf_bf;  // split-BF16 tables (forward / inverse layouts)
@@ -61,7 +59,7 @@ struct GroupDev {
 
 // ---- work-list kernels ----
 
-// Ring tasks come in two lists, one per ring kernel family, and every
+// Ring tasks are those of the register-resident kernels, and every
 // contraction launch carries one shape class (row tiles RTC, degree groups
 // LQC / LQ2C) and holds only that class's bodies, so that each work-list
 // kernel keeps the register budget of its single-B counterpart.  W is the
@@ -98,25 +96,6 @@ __global__ __launch_bounds__(FAST_NT, fast_waves_per_simd<T>()) void ring_fast_w
       SU2_FAST_CASE(128)
     }
 #undef SU2_FAST_CASE
-    __syncthreads();
-  }
-}
-
-template <class T, bool FWD>
-__global__ __launch_bounds__(GENERIC_NT) void ring_generic_worklist_kernel(const WorkItem* __restrict__ items, int n,
-                                                                            const GroupDev<T>* __restrict__ groups,
-                                                                            const cpx<T>* __restrict__ in,
-                                                                            cpx<T>* __restrict__ out, int dir) {
-  extern __shared__ __align__(16) unsigned char smem[];
-  for (int it = blockIdx.x; it < n; it += gridDim.x) {
-    const WorkItem w = items[it];
-    const RingParams<T>& p = groups[w.g].rp[dir];
-    if constexpr (FWD)
-      ring_forward_any<T>(in, ring_offset(p.soff, w.a, p.N) + (size_t)w.b * p.N * p.N, groups[w.g].S, p, w.a, w.b,
-                          smem);
-    else
-      ring_inverse_any<T>(groups[w.g].S, out, ring_offset(p.soff, w.a, p.N) + (size_t)w.b * p.N * p.N, p, w.a, w.b,
-                          smem);
     __syncthreads();
   }
 }
@@ -218,13 +197,13 @@ struct MixedState {
   std::vector<int> group_B;
   long long total_samples = 0, total_coeffs = 0;
   void* d_groups = nullptr;         // GroupDev<T>[groups]
-  su2::WorkItem* d_ringf = nullptr;   // ring tasks of the register-resident N = 128 kernels
-  su2::WorkItem* d_ringg = nullptr;   // ring tasks of the generic kernels
+  su2::WorkItem* d_ringf = nullptr;   // ring tasks of the register-resident kernels
   su2::WorkItem* d_betaf = nullptr;
   su2::WorkItem* d_betai = nullptr;
-  int n_ringf = 0, n_ringg = 0, n_betaf = 0, n_betai = 0;
-  // groups whose rings (N = 256) run the single-B plan's dedicated kernels
-  // (one-pass sliced in FP32, two-pass in FP64) instead of a work list
+  int n_ringf = 0, n_betaf = 0, n_betai = 0;
+  // groups whose rings run the single-B plan's own launches instead of a work
+  // list: the mixed-radix kernels, and N = 256 (one-pass sliced in FP32,
+  // two-pass in FP64)
   std::vector<int> dedicated;
   // the contraction lists in runs of one shape class (forward: row tiles;
   // inverse: degrees per group), largest class first: a run is one launch of
@@ -239,7 +218,7 @@ struct MixedState {
     int cls, w, begin, n;  // w: tile widths held (1: 16 signals, 2: widest, 3: both)
   };
   std::vector<Run> runs_f, runs_i;
-  size_t smem_ringf = 0, smem_ringg = 0, smem_betaf = 0, smem_betai = 0;
+  size_t smem_ringf = 0, smem_betaf = 0, smem_betai = 0;
   int rtmax = 1;                    // largest forward row-tile count present (LDS check)
   int num_cu = 0;
   // workgroups per CU (0: one per task): ring forward, contraction forward,
@@ -251,7 +230,7 @@ struct MixedState {
   std::vector<int> narrow_f, narrow_i;
   int max_betaf = 0, max_betai = 0;  // work-list capacities (every group in 16-signal tiles)
   hipStream_t cap = nullptr;          // capture stream
-  hipStream_t side = nullptr;         // second branch: generic and N = 256 rings beside the fast ones
+  hipStream_t side = nullptr;         // second branch: mixed-radix and N = 256 rings beside the fast ones
   hipEvent_t fork = nullptr, join = nullptr;
   std::vector<MixedGraph> graphs;
   std::vector<void*> allocs;
@@ -272,10 +251,6 @@ template <class T>
 void* ringf_kernel_ptr(bool fwd, bool real) {
   if (real) return fwd ? (void*)ring_fast_worklist_kernel<T, true, true> : (void*)ring_fast_worklist_kernel<T, false, true>;
   return fwd ? (void*)ring_fast_worklist_kernel<T, true, false> : (void*)ring_fast_worklist_kernel<T, false, false>;
-}
-template <class T>
-void* ringg_kernel_ptr(bool fwd) {
-  return fwd ? (void*)ring_generic_worklist_kernel<T, true> : (void*)ring_generic_worklist_kernel<T, false>;
 }
 
 template <class T, int KC, int W>
@@ -346,11 +321,14 @@ int wgs_per_cu(const void* f, int threads, size_t smem, int device) {
   return n;
 }
 
-// the rings of an N = 256 group with the single-B plan's kernels (d: 0
-// forward, 1 inverse, 2 adjoint); the ring spectra are the group's workspace
+// the rings of a mixed-radix or N = 256 group with the single-B plan's kernels
+// (d: 0 forward, 1 inverse, 2 adjoint); the ring spectra are the group's workspace
 template <class T>
-hipError_t launch_rings_256(su2_plan_s* gp, bool fwd, int d, const void* in, void* out, hipStream_t s) {
+hipError_t launch_group_rings(su2_plan_s* gp, bool fwd, int d, const void* in, void* out, hipStream_t s) {
   cpx<T>* S = (cpx<T>*)gp->d_S;
+  if (!gp->large)
+    return fwd ? launch_ring_forward_radix<T>(radix_params<T>(gp, 0), (const cpx<T>*)in, S, s)
+               : launch_ring_inverse_radix<T>(radix_params<T>(gp, d == 2), S, (cpx<T>*)out, s);
   if (gp->sliced) {
     if constexpr (std::is_same<T, float>::value)
       return fwd ? launch_ring_sliced4(true, fast_params<T>(gp, 0), (const cpx<T>*)in, S, s)
@@ -372,11 +350,10 @@ hipError_t enqueue(su2_plan_s* pl, int which, int dir, const void* in, void* out
   switch (which) {
     case 0:
     case 3: {
-      // the generic list and the N = 256 groups run on a second branch beside
+      // the groups with launches of their own run on a second branch beside
       // the register-resident list (fork/join through events, also inside a
       // stream capture)
-      const bool side_work = ms->n_ringg > 0 || !ms->dedicated.empty();
-      const bool both = ms->n_ringf > 0 && side_work;
+      const bool both = ms->n_ringf > 0 && !ms->dedicated.empty();
       hipStream_t sg = both ? ms->side : s;
       hipError_t e;
       if (both) {
@@ -387,15 +364,8 @@ hipError_t enqueue(su2_plan_s* pl, int which, int dir, const void* in, void* out
       const cpx<T>* xin = (const cpx<T>*)in;
       cpx<T>* xout = (cpx<T>*)out;
       void* args[] = {nullptr, nullptr, (void*)&g, (void*)&xin, (void*)&xout, (void*)&d};
-      if (ms->n_ringg > 0) {
-        args[0] = (void*)&ms->d_ringg;
-        args[1] = (void*)&ms->n_ringg;
-        if ((e = hipLaunchKernel(ringg_kernel_ptr<T>(which == 0), grid_of(ms->n_ringg), dim3(GENERIC_NT), args,
-                                 ms->smem_ringg, sg)) != hipSuccess)
-          return e;
-      }
       for (int gi : ms->dedicated)
-        if ((e = launch_rings_256<T>(ms->groups[gi], which == 0, d, in, out, sg)) != hipSuccess) return e;
+        if ((e = launch_group_rings<T>(ms->groups[gi], which == 0, d, in, out, sg)) != hipSuccess) return e;
       if (ms->n_ringf > 0) {
         args[0] = (void*)&ms->d_ringf;
         args[1] = (void*)&ms->n_ringf;
@@ -475,8 +445,7 @@ hipError_t set_worklist_smem(su2_plan_s* pl) {
   int max_lds = 0;
   hipError_t e = hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, pl->device);
   if (e != hipSuccess) return e;
-  if (ms->smem_ringf > (size_t)max_lds || ms->smem_ringg > (size_t)max_lds || ms->smem_betaf > (size_t)max_lds ||
-      ms->smem_betai > (size_t)max_lds)
+  if (ms->smem_ringf > (size_t)max_lds || ms->smem_betaf > (size_t)max_lds || ms->smem_betai > (size_t)max_lds)
     return hipErrorInvalidValue;
   for (const MixedState::Run& r : ms->runs_f)
     if ((e = hipFuncSetAttribute(bf ? betaf_bf16_kernel_ptr(r.cls) : betaf_kernel_ptr<T>(r.cls, ms->kc, r.w),
@@ -489,9 +458,6 @@ hipError_t set_worklist_smem(su2_plan_s* pl) {
   for (int fwd = 0; fwd < 2; fwd++) {
     if ((e = hipFuncSetAttribute(ringf_kernel_ptr<T>(fwd, pl->real), hipFuncAttributeMaxDynamicSharedMemorySize,
                                  max_lds)) != hipSuccess)
-      return e;
-    if ((e = hipFuncSetAttribute(ringg_kernel_ptr<T>(fwd), hipFuncAttributeMaxDynamicSharedMemorySize, max_lds)) !=
-        hipSuccess)
       return e;
   }
   return hipSuccess;
@@ -518,7 +484,7 @@ su2_status_t build_worklists(su2_plan_s* pl, int only_group = -1) {
     ms->kc = fwd_kc_default<T>();
   }
   std::vector<GroupDev<T>> hg(ng);
-  std::vector<std::pair<double, WorkItem>> ringf, ringg, betaf, betai;
+  std::vector<std::pair<double, WorkItem>> ringf, betaf, betai;
   int cap_f = 0, cap_i = 0;
   ms->rtmax = 1;
   ms->dedicated.clear();
@@ -534,7 +500,6 @@ su2_status_t build_worklists(su2_plan_s* pl, int only_group = -1) {
     d.narrow_i = ms->narrow_i[gi];
     const T* tab = std::is_same<T, double>::value ? (const T*)gp->d_tab64 : (const T*)gp->d_tab32;
     for (int dir = 0; dir < 3; dir++) {
-      d.rp[dir] = ring_params<T>(gp, dir == 2);
       d.fp[dir] = fast_params<T>(gp, dir == 2);
       d.bp[dir] = beta_params<T>(gp, tab, dir == 2);
     }
@@ -545,18 +510,14 @@ su2_status_t build_worklists(su2_plan_s* pl, int only_group = -1) {
     const int N = gp->N;
     // ring LDS
     const double ring_cost = (double)N * N * (N > 1 ? std::log2((double)N) : 1.0);
-    if (gp->large) {
-      ms->dedicated.push_back(gi);  // launched whole by launch_rings_256
-    } else if (gp->fast) {
+    if (!gp->fast) {
+      ms->dedicated.push_back(gi);  // launched whole by launch_group_rings
+    } else {
       // one task per workgroup's worth of consecutive rings of a signal
       ms->smem_ringf = std::max(ms->smem_ringf, fast_ring_smem<T>(N));
       const int rpw = fast_rings_per_group(N);
       for (int i = 0; i < gp->batch; i++)
         for (int k = 0; k < N; k += rpw) ringf.push_back({ring_cost * rpw, WorkItem{gi, i, k}});
-    } else {
-      ms->smem_ringg = std::max(ms->smem_ringg, ring_smem_bytes<T>(d.rp[0]));
-      for (int i = 0; i < gp->batch; i++)
-        for (int k = 0; k < N; k++) ringg.push_back({ring_cost, WorkItem{gi, i, k}});
     }
     const int btf = bf ? XBF_BT : (d.narrow_f ? 16 : BetaCfg<T>::BT);
     const int bti = d.narrow_i ? 16 : (bf ? XB_BT : BetaCfg<T>::BT);
@@ -587,7 +548,6 @@ su2_status_t build_worklists(su2_plan_s* pl, int only_group = -1) {
     ms->max_betai = cap_i;
     if ((e = mixed_alloc(ms, &ms->d_groups, sizeof(GroupDev<T>) * ng)) != hipSuccess) return hip_fail(e);
     if ((e = mixed_alloc(ms, (void**)&ms->d_ringf, sizeof(WorkItem) * ringf.size())) != hipSuccess) return hip_fail(e);
-    if ((e = mixed_alloc(ms, (void**)&ms->d_ringg, sizeof(WorkItem) * ringg.size())) != hipSuccess) return hip_fail(e);
     if ((e = mixed_alloc(ms, (void**)&ms->d_betaf, sizeof(WorkItem) * cap_f)) != hipSuccess) return hip_fail(e);
     if ((e = mixed_alloc(ms, (void**)&ms->d_betai, sizeof(WorkItem) * cap_i)) != hipSuccess) return hip_fail(e);
   }
@@ -603,7 +563,6 @@ su2_status_t build_worklists(su2_plan_s* pl, int only_group = -1) {
     return v.empty() ? hipSuccess : hipMemcpy(dst, v.data(), sizeof(WorkItem) * v.size(), hipMemcpyHostToDevice);
   };
   if ((e = upload(ringf, ms->d_ringf, &ms->n_ringf)) != hipSuccess) return hip_fail(e);
-  if ((e = upload(ringg, ms->d_ringg, &ms->n_ringg)) != hipSuccess) return hip_fail(e);
   // contraction lists: by class (largest first), then by tile width where a
   // class is split (widest first), then by decreasing cost; one run per class
   // and width set

@@ -16,10 +16,7 @@ using namespace su2;
 struct su2_plan_s {
   int B = 0, N = 0, batch = 0;
   su2_dtype_t dtype = SU2_C128;
-  int split = 1, Nc = 0;
   int P = 0, P_pad = 0, ntiles = 0;
-  int nrad_c = 0, nrad_n = 0, rad_c[MAX_RADICES] = {0}, rad_n[MAX_RADICES] = {0};
-  int cls_begin[MAX_SPLIT] = {0}, cls_end[MAX_SPLIT] = {0};
   long long ncoef = 0;
   long long tab_elems = 0;
   int device = 0;
@@ -33,8 +30,6 @@ struct su2_plan_s {
   long long itab_elems = 0;
   bf16x2_t* d_tabbf = nullptr;
   unsigned* d_tabbf_fwd = nullptr;
-  int* d_fftpos = nullptr;
-  int* d_colq = nullptr;
   int* d_bins = nullptr;
   bool fast = false;
   int rbeg[FAST_ROUNDS] = {0}, rend[FAST_ROUNDS] = {0};
@@ -45,7 +40,7 @@ struct su2_plan_s {
   bool sym = false;             // point-symmetric pair layout, upper tiles share the lower tiles' table blocks
   bool real = false;            // real-signal plan
   // real-signal plan on the complex kernels (rings without a half-spectrum
-  // form: generic and N = 256): real samples in, real part out, every pair
+  // form: mixed-radix and N = 256): real samples in, real part out, every pair
   // contracted; otherwise a real plan forms and contracts only the pairs
   // with 2m > 0, or 2m = 0 and 2n >= 0
   bool real_io = false;
@@ -56,11 +51,12 @@ struct su2_plan_s {
   double* d_nodes = nullptr;  // [3][N]: cos(beta_k), cos(beta_k / 2), sin(beta_k / 2)
   bool large = false;            // N = 256: two-pass ring kernels through an intermediate (d_G)
   bool sliced = false;          // N = 256 in FP32: both ring directions run in one pass, four workgroups per ring
-  int* d_cols = nullptr;        // N = 256 in FP32: per-column bin bases of the one-pass rings (null: not usable)
+  // per-column bin bases: the mixed-radix rings' RadixRingParams::cols, or
+  // (N = 256 in FP32) FastRingParams::cols of the one-pass rings (null: not usable)
+  int* d_cols = nullptr;
   int* d_qrange = nullptr;
   void* d_G = nullptr;
   int large_chunk = 0;
-  void* d_rho = nullptr;
   void* d_tw = nullptr;
   void* d_W = nullptr;
   void* d_S = nullptr;
@@ -98,18 +94,13 @@ void mixed_tuning(const su2_plan_s* pl, int32_t* knobs);
 int mixed_shapes(const su2_plan_s* pl, int32_t* out, int32_t capacity);  // groups; fills 4 int32 per group
 
 template <class T>
-RingParams<T> ring_params(const su2_plan_s* pl, int adjoint) {
-  RingParams<T> r;
+RadixRingParams<T> radix_params(const su2_plan_s* pl, int adjoint) {
+  RadixRingParams<T> r;
   memset(&r, 0, sizeof(r));
-  r.N = pl->N; r.Nc = pl->Nc; r.split = pl->split; r.batch = pl->batch; r.ntiles = pl->ntiles;
-  r.nrad_c = pl->nrad_c; r.nrad_n = pl->nrad_n;
-  for (int i = 0; i < MAX_RADICES; i++) { r.rad_c[i] = pl->rad_c[i]; r.rad_n[i] = pl->rad_n[i]; }
-  for (int i = 0; i < MAX_SPLIT; i++) { r.cls_begin[i] = pl->cls_begin[i]; r.cls_end[i] = pl->cls_end[i]; }
+  r.N = pl->N; r.batch = pl->batch;
   r.tw = (const cpx<T>*)pl->d_tw;
   r.W = (const T*)pl->d_W;
-  r.fftpos = pl->d_fftpos;
-  r.rho = (const cpx<T>*)pl->d_rho;
-  r.colq = pl->d_colq;
+  r.cols = (const int4*)pl->d_cols;
   r.adjoint = adjoint;
   r.soff = pl->d_soff;
   r.so3 = pl->so3 ? 1 : 0;
@@ -183,7 +174,10 @@ BetaParams<T> beta_params(const su2_plan_s* pl, const T* tab, int scale_mode) {
   b.tile0 = half ? pl->rbeg[0] / PT : 0;
   b.so3 = pl->so3 ? 1 : 0;
   b.table_signs = pl->sym ? 1 : 0;
-  b.paired = (pl->sym && b.tile0 == 0) ? 1 : 0;
+  // (mixed-radix plans keep the natural order: with few tiles the mirror
+  // pairs spread unevenly over the XCDs, B = 24, 151 signals 26.7 against
+  // 19.6 us, and B = 48 and 96 gained nothing either)
+  b.paired = (pl->sym && b.tile0 == 0 && (pl->fast || pl->large)) ? 1 : 0;
   return b;
 }
 
