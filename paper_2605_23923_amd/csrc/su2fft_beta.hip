@@ -12,45 +12,16 @@
 // ring side).  The phases were applied on the ring side.
 //
 // Both are small dense GEMMs per pair, run on the matrix cores
-// (V_MFMA_F32_16X16X4_F32 / V_MFMA_F64_16X16X4_F64; 16x4 by 4x16 blocks).
-// Operand layout per 64-lane wave: A[i][kk] in lane i + 16 kk, B[kk][j] in
-// lane j + 16 kk.  Accumulator element r of lane (j + 16 g) is D[4 g + r][j]
-// for the FP32 instruction and D[g + 4 r][j] for the FP64 one (both measured).
-#include "su2fft_internal.h"
+// (operand layouts: su2fft_mfma.h).  Small batches run the streaming kernels
+// of su2fft_beta_small.hip instead, with the same products in the same order.
+#include "su2fft_mfma.h"
 
 namespace su2 {
 
-typedef float floatx4 __attribute__((ext_vector_type(4)));
-typedef double doublex4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 // word 3 of a raw buffer resource on CDNA (gfx9 family): 32-bit data format,
 // no swizzle; range checking against word 2 (bytes) with stride 0
 constexpr int BUFFER_RSRC_WORD3 = 0x00020000;
-
-template <class T>
-struct acc4;
-template <>
-struct acc4<float> {
-  typedef floatx4 type;
-};
-template <>
-struct acc4<double> {
-  typedef doublex4 type;
-};
-
-__device__ __forceinline__ floatx4 mfma16x16x4(float a, float b, floatx4 c) {
-  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-}
-__device__ __forceinline__ doublex4 mfma16x16x4(double a, double b, doublex4 c) {
-  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-}
-
-template <class T>
-__device__ __forceinline__ int acc_row(int lane, int r);
-template <>
-__device__ __forceinline__ int acc_row<float>(int lane, int r) { return 4 * (lane >> 4) + r; }
-template <>
-__device__ __forceinline__ int acc_row<double>(int lane, int r) { return (lane >> 4) + 4 * r; }
 
 template <class T>
 struct BetaCfg;
@@ -62,19 +33,6 @@ template <>
 struct BetaCfg<double> {
   static constexpr int BT = 16;  // 32 real columns
 };
-
-// compute units of the current device (read once per process)
-inline int device_cus() {
-  static int cus = 0;
-  if (cus == 0) {
-    int dev = 0, n = 0;
-    cus = (hipGetDevice(&dev) == hipSuccess &&
-           hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && n > 0)
-              ? n
-              : 256;
-  }
-  return cus;
-}
 
 // ---- coefficients through LDS ----
 //
@@ -598,6 +556,7 @@ bool narrow_tiles(const BetaParams<T>& p, int units) {
 
 template <class T>
 hipError_t launch_beta_forward(const BetaParams<T>& p, const cpx<T>* S, cpx<T>* coeffs, hipStream_t s) {
+  if (beta_small_forward<T>(p)) return launch_beta_forward_small<T>(p, S, coeffs, s);
   constexpr int BTW = BetaCfg<T>::BT;      // widest signal tile
   constexpr int BTN = BTW > 16 ? 16 : BTW;  // narrow tiles (narrow_tiles)
   const int rt = beta_rtmax(p.B);
@@ -615,6 +574,7 @@ hipError_t launch_beta_forward(const BetaParams<T>& p, const cpx<T>* S, cpx<T>* 
 
 template <class T>
 hipError_t launch_beta_inverse(const BetaParams<T>& p, const cpx<T>* coeffs, cpx<T>* S, hipStream_t s) {
+  if (beta_small_inverse<T>(p)) return launch_beta_inverse_small<T>(p, coeffs, S, s);
   constexpr int BTW = BetaCfg<T>::BT;                             // widest signal tile
   constexpr int BTN = BTW > 16 ? 16 : BTW;                         // narrow tiles (narrow_tiles)
   const int bt = narrow_tiles(p, p.ntiles - p.tile0) ? BTN : BTW;

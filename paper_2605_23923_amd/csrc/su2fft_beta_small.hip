@@ -1,0 +1,594 @@
+// The beta contractions (su2fft_beta.hip) for small batches: the same products
+// in the same order, hence the same bits, streamed straight into the matrix
+// cores.
+//
+// With few signals the Wigner-d table is most of the bytes and the tile
+// kernels lose twice: their 16- or 32-signal tiles leave most matrix-core
+// columns empty, and one staged chunk per workgroup keeps too few bytes in
+// flight.  Here a wave owns one pair (m, n) together with its mirror
+// (-m, -n), which uses the same table column up to sign: the columns of one
+// 16-wide product are 2 pairs x 4 signals x (re, im) (CT products side by side
+// for more signals), every table value is read once per launch, by coalesced
+// loads that go directly into operand registers, many of them in flight, and
+// the forward has no LDS and no barrier at all.  Plans without the symmetric
+// pair list, and half-spectrum real plans (whose mirrors carry no spectra),
+// take one pair per wave and twice the signals per product.
+#include "su2fft_mfma.h"
+
+namespace su2 {
+
+// column cc of a wave's products: which of its MIR pairs, which signal of the
+// tile's BT, and re or im
+template <int MIR, int CT>
+struct SmallCols {
+  static constexpr int BT = 8 * CT / MIR;
+  __device__ static __forceinline__ int mir(int cc) { return cc / (2 * BT); }
+  __device__ static __forceinline__ int sig(int cc) { return cc % (2 * BT) / 2; }
+};
+
+// What the kernels need of the wave's pair at list position `at` and of its
+// mirror, and the table column the products read: the pair's own, or its
+// mirror's where the pair is a pad.
+template <class T, int MIR>
+struct SmallPairs {
+  struct Pair {
+    int tm, tn, tl0, L, tsign;
+  };
+  Pair q0, q1;
+  int pos0, pos1, L, lsum;
+  long long tab, itab;  // the column's first value in the row-major and the inverse-layout table
+  __device__ __forceinline__ SmallPairs(const BetaParams<T>& p, int at) {
+    pos0 = at;
+    pos1 = MIR == 2 ? p.ntiles * PT - 1 - at : at;
+    const PairInfo a = p.pairs[pos0], b = p.pairs[pos1];
+    q0 = {a.tm, a.tn, a.tl0, a.L, a.tsign};
+    q1 = {b.tm, b.tn, b.tl0, b.L, b.tsign};
+    if (p.real && mirrored_pair(a.tm, a.tn)) q0.L = q1.L = 0;
+    const bool own = q0.L > 0;
+    // the self-mirror middle tile stores both columns of a couple (2m = 0: the
+    // same values up to sign); reading the first, the second needs its sign
+    if (MIR == 2 && own && b.towner) q1.tsign = (((b.tm - b.tn) / 2) & 1) ? -1 : 1;
+    L = own ? q0.L : q1.L;
+    lsum = own ? a.lsum : b.lsum;
+    tab = own ? a.tab + a.coff : b.tab + b.coff;
+    itab = own ? a.itab : b.itab;
+  }
+  __device__ __forceinline__ Pair pick(int mir) const {
+    if (MIR == 1) return q0;
+    return {mir ? q1.tm : q0.tm, mir ? q1.tn : q0.tn, mir ? q1.tl0 : q0.tl0, mir ? q1.L : q0.L,
+            mir ? q1.tsign : q0.tsign};
+  }
+};
+
+// Forward: fhat(l)_{mn}[b] = sum_k d^l(beta_k) S_k(m, n)[b].  One wave per
+// pair (and mirror): table rows as the A operand, spectra as the B operand,
+// KU groups of 4 nodes requested together.  RT row tiles cover the pair's L
+// degrees, degree RT i + rt in row i of tile rt, so that a lane's values of
+// all row tiles are adjacent and come in one load.
+constexpr int SMALL_FWD_WAVES = 4;  // waves (pairs) per workgroup: a quarter of a tile
+
+// a wave's sums out to the coefficient vectors
+template <class T, int RT, int CT, int MIR>
+__device__ __forceinline__ void store_forward_small(cpx<T>* __restrict__ coeffs, const BetaParams<T>& p,
+                                                    const SmallPairs<T, MIR>& w, int b0, int lane,
+                                                    const typename acc4<T>::type (&acc)[RT][CT]) {
+  typedef SmallCols<MIR, CT> Cols;
+  const int lrow = lane & 15;
+#pragma unroll
+  for (int ct = 0; ct < CT; ct++) {
+    const int cc = ct * 16 + lrow, b = b0 + Cols::sig(cc);
+    const auto q = w.pick(Cols::mir(cc));
+    if (b >= p.batch) continue;
+    const T ts = p.table_signs && q.tsign < 0 ? T(-1) : T(1);
+    T* out = reinterpret_cast<T*>(coeffs + coef_offset(p.coff, b, p.ncoef)) + (cc & 1);
+    // half-spectrum real plans also write the mirror (-1)^{m-n} conj(fhat) at (-m, -n)
+    const bool mirror = MIR == 1 && p.real && (q.tm != 0 || q.tn != 0);
+    const T sg = ((((q.tm - q.tn) / 2) & 1) ? T(-1) : T(1)) * ((cc & 1) ? T(-1) : T(1));
+#pragma unroll
+    for (int rt = 0; rt < RT; rt++)
+#pragma unroll
+      for (int r = 0; r < 4; r++) {
+        const int j = RT * acc_row<T>(lane, r) + rt;
+        if (j >= q.L) continue;
+        const T v = ts * acc[rt][ct][r];
+        out[2 * coef_index_of(p.so3, q.tl0 + 2 * j, q.tm, q.tn)] = v;
+        if (mirror) out[2 * coef_index_of(p.so3, q.tl0 + 2 * j, -q.tm, -q.tn)] = sg * v;
+      }
+  }
+}
+
+template <class T, int RT, int CT, int MIR>
+__device__ __forceinline__ void beta_forward_small_pair(const cpx<T>* __restrict__ S, cpx<T>* __restrict__ coeffs,
+                                                        const BetaParams<T>& p, const SmallPairs<T, MIR>& w, int b0,
+                                                        int lane) {
+  typedef typename acc4<T>::type accT;
+  typedef SmallCols<MIR, CT> Cols;
+  // RT adjacent table values, at any element's alignment
+  typedef T rowv __attribute__((ext_vector_type(RT), aligned(sizeof(T))));
+  constexpr int KU = RT == 1 ? (sizeof(T) == 4 ? 16 : 8) : (RT == 2 ? 8 : 4);
+  const int lrow = lane & 15, lk = lane >> 4, N = p.N;
+  // operand addresses of node lk.  Rows past L read the columns after the
+  // pair's (or the padding after the table) and are dropped; signals past the
+  // batch read the last one and are dropped likewise.
+  const T* ta = p.tab + w.tab + (long long)lk * w.lsum + RT * lrow;
+  const T* tb[CT];
+#pragma unroll
+  for (int ct = 0; ct < CT; ct++) {
+    const int cc = ct * 16 + lrow, pos = MIR == 2 && Cols::mir(cc) ? w.pos1 : w.pos0;
+    const int b = min(b0 + Cols::sig(cc), p.batch - 1);
+    tb[ct] = reinterpret_cast<const T*>(S + (((size_t)(pos / PT) * N + lk) * p.batch + b) * PT + pos % PT) + (cc & 1);
+  }
+  const long long sa = 4LL * w.lsum, sb = 8LL * p.batch * PT;
+
+  accT acc[RT][CT];
+#pragma unroll
+  for (int rt = 0; rt < RT; rt++)
+#pragma unroll
+    for (int ct = 0; ct < CT; ct++)
+#pragma unroll
+      for (int r = 0; r < 4; r++) acc[rt][ct][r] = T(0);
+
+  auto load = [&](rowv& a, T (&b)[CT]) {
+    a = *reinterpret_cast<const rowv*>(ta);
+    ta += sa;
+#pragma unroll
+    for (int ct = 0; ct < CT; ct++) {
+      b[ct] = *tb[ct];
+      tb[ct] += sb;
+    }
+  };
+  auto products = [&](const rowv& a, const T (&b)[CT]) {
+#pragma unroll
+    for (int rt = 0; rt < RT; rt++)
+#pragma unroll
+      for (int ct = 0; ct < CT; ct++) acc[rt][ct] = mfma16x16x4(a[rt], b[ct], acc[rt][ct]);
+  };
+  const int ng = N / 4;  // whole groups of 4 nodes
+  int g = 0;
+  for (; g + KU <= ng; g += KU) {
+    rowv a[KU];
+    T b[KU][CT];
+#pragma unroll
+    for (int u = 0; u < KU; u++) load(a[u], b[u]);
+#pragma unroll
+    for (int u = 0; u < KU; u++) products(a[u], b[u]);
+  }
+  if constexpr (KU > 4)
+    for (; g + 4 <= ng; g += 4) {
+      rowv a[4];
+      T b[4][CT];
+#pragma unroll
+      for (int u = 0; u < 4; u++) load(a[u], b[u]);
+#pragma unroll
+      for (int u = 0; u < 4; u++) products(a[u], b[u]);
+    }
+  for (; g < ng; g++) {
+    rowv a;
+    T b[CT];
+    load(a, b);
+    products(a, b);
+  }
+  if (N % 4 != 0) {  // the last N mod 4 nodes, zeros past them
+    const bool in = 4 * ng + lk < N;
+    rowv a;
+    T b[CT];
+#pragma unroll
+    for (int rt = 0; rt < RT; rt++) a[rt] = in ? ta[rt] : T(0);
+#pragma unroll
+    for (int ct = 0; ct < CT; ct++) b[ct] = in ? *tb[ct] : T(0);
+    products(a, b);
+  }
+
+  store_forward_small<T, RT, CT, MIR>(coeffs, p, w, b0, lane, acc);
+}
+
+// RTMAX: row tiles of the plan's longest pairs (beta_rtmax)
+template <class T, int RTMAX, int CT, int MIR>
+__global__ __launch_bounds__(64 * SMALL_FWD_WAVES) void beta_forward_small_kernel(const cpx<T>* __restrict__ S,
+                                                                                  cpx<T>* __restrict__ coeffs,
+                                                                                  BetaParams<T> p, int pos_end) {
+  constexpr int BT = SmallCols<MIR, CT>::BT, QT = PT / SMALL_FWD_WAVES;
+  const int nbt = (p.batch + BT - 1) / BT;
+  const int ntl = (pos_end - p.tile0 * PT + PT - 1) / PT;
+  const TileSlot sl = contraction_slot(blockIdx.x, ntl, QT * nbt);
+  if (!sl.valid) return;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int at = (p.tile0 + sl.tile) * PT + (sl.bt % QT) * SMALL_FWD_WAVES + wave, b0 = sl.bt / QT * BT;
+  if (at >= pos_end) return;
+  const SmallPairs<T, MIR> w(p, at);
+  if (w.L == 0) return;
+  const int rt = (w.L + 15) / 16;  // uniform
+  if constexpr (RTMAX >= 4) {
+    if (rt == 4) return beta_forward_small_pair<T, 4, CT, MIR>(S, coeffs, p, w, b0, lane);
+    if (rt == 3) return beta_forward_small_pair<T, 3, CT, MIR>(S, coeffs, p, w, b0, lane);
+  }
+  if constexpr (RTMAX >= 2)
+    if (rt == 2) return beta_forward_small_pair<T, 2, CT, MIR>(S, coeffs, p, w, b0, lane);
+  beta_forward_small_pair<T, 1, CT, MIR>(S, coeffs, p, w, b0, lane);
+}
+
+// Forward with the spectra through LDS, from a few signals on: a wave that
+// reads its own pair's values touches a 128-byte line of S per node and signal
+// for 8 of its bytes, which soon costs more than the table.  One workgroup of
+// 16 waves per pair tile (and its mirror tile) reads whole lines, KG groups of
+// 4 nodes at a time into one of two buffers; table values still go straight
+// to registers.
+constexpr int MID_THREADS = 64 * PT;
+
+template <class T, int RTMAX, int CT, int MIR>
+struct MidShape {
+  static constexpr int BT = SmallCols<MIR, CT>::BT;
+  // 70 KB for the two buffers, two workgroups per CU (half of it where the
+  // operands of 64 degrees need the registers)
+  static constexpr int KG = sizeof(T) == 4 ? (RTMAX == 4 && CT == 1 ? 4 : 8 / CT) : 4 / CT;
+  static constexpr int KN = 4 * KG;
+  static constexpr int PB = 2 * PT + 2, HALF = KN * BT * PB + 2;  // one of the MIR tiles' rows
+  static constexpr int VC = 16 / (int)sizeof(cpx<T>), VPR = PT / VC;  // 16-byte vectors per row
+  static constexpr int NV = MIR * KN * BT * VPR, VPT = (NV + MID_THREADS - 1) / MID_THREADS;
+};
+
+template <class T, int RTMAX, int RT, int CT, int MIR>
+__device__ __forceinline__ void beta_forward_mid_body(const cpx<T>* __restrict__ S, cpx<T>* __restrict__ coeffs,
+                                                      const BetaParams<T>& p, const SmallPairs<T, MIR>& w, int tile,
+                                                      int b0, T* lds, int wave, int lane) {
+  typedef typename acc4<T>::type accT;
+  typedef SmallCols<MIR, CT> Cols;
+  typedef MidShape<T, RTMAX, CT, MIR> MS;
+  typedef T rowv __attribute__((ext_vector_type(RT), aligned(sizeof(T))));
+  typedef T vec16 __attribute__((ext_vector_type(16 / sizeof(T))));
+  constexpr int KG = MS::KG, KN = MS::KN, BT = MS::BT;
+  const int lrow = lane & 15, lk = lane >> 4, N = p.N, tid = wave * 64 + lane;
+  const int nb = min(BT, p.batch - b0), ng = (N + 3) / 4, nchunk = (ng + KG - 1) / KG;
+  const bool work = w.L > 0;
+
+  // this thread's 16-byte pieces of a chunk of S: row (mir, node, signal), piece pv
+  vec16 sv[MS::VPT];
+  auto fetch_s = [&](int c) {
+#pragma unroll
+    for (int i = 0; i < MS::VPT; i++) {
+      const int v = tid + MID_THREADS * i, pv = v % MS::VPR, bb = v / MS::VPR % BT, kk = v / (MS::VPR * BT) % KN;
+      const int mir = v / (MS::VPR * BT * KN), k = c * KN + kk, t = mir ? p.ntiles - 1 - tile : tile;
+      sv[i] = vec16(T(0));
+      if (v < MS::NV && k < N && bb < nb)
+        sv[i] = *reinterpret_cast<const vec16*>(S + (((size_t)t * N + k) * p.batch + b0 + bb) * PT + pv * MS::VC);
+    }
+  };
+  auto commit_s = [&](int c) {
+    T* d = lds + (c & 1) * MIR * MS::HALF;
+#pragma unroll
+    for (int i = 0; i < MS::VPT; i++) {
+      const int v = tid + MID_THREADS * i, pv = v % MS::VPR, bb = v / MS::VPR % BT, kk = v / (MS::VPR * BT) % KN;
+      const int mir = v / (MS::VPR * BT * KN);
+      if (v < MS::NV)
+#pragma unroll
+        for (int e = 0; e < 2 * MS::VC; e++) d[mir * MS::HALF + (kk * BT + bb) * MS::PB + 2 * pv * MS::VC + e] = sv[i][e];
+    }
+  };
+  rowv a[KG];
+  const T* ta = p.tab + w.tab + (long long)lk * w.lsum + RT * lrow;
+  const long long sa = 4LL * w.lsum;
+  auto fetch_a = [&](int c) {
+#pragma unroll
+    for (int u = 0; u < KG; u++) {
+      const int g = c * KG + u;
+#pragma unroll
+      for (int rt = 0; rt < RT; rt++) a[u][rt] = T(0);
+      if (work && 4 * g + lk < N) a[u] = *reinterpret_cast<const rowv*>(ta + g * sa);
+    }
+  };
+  int bofs[CT];
+#pragma unroll
+  for (int ct = 0; ct < CT; ct++) {
+    const int cc = ct * 16 + lrow, mir = MIR == 2 ? Cols::mir(cc) : 0;
+    bofs[ct] = mir * MS::HALF + (lk * BT + Cols::sig(cc)) * MS::PB + 2 * (mir ? PT - 1 - wave : wave) + (cc & 1);
+  }
+
+  accT acc[RT][CT];
+#pragma unroll
+  for (int rt = 0; rt < RT; rt++)
+#pragma unroll
+    for (int ct = 0; ct < CT; ct++)
+#pragma unroll
+      for (int r = 0; r < 4; r++) acc[rt][ct][r] = T(0);
+  fetch_s(0);
+  fetch_a(0);
+  commit_s(0);
+  __syncthreads();
+  for (int c = 0; c < nchunk; c++) {
+    if (c + 1 < nchunk) fetch_s(c + 1);
+    const T* src = lds + (c & 1) * MIR * MS::HALF;
+    if (work) {
+#pragma unroll
+      for (int u = 0; u < KG; u++) {
+        if (c * KG + u >= ng) break;
+        T b[CT];
+#pragma unroll
+        for (int ct = 0; ct < CT; ct++) b[ct] = src[bofs[ct] + 4 * u * BT * MS::PB];
+#pragma unroll
+        for (int rt = 0; rt < RT; rt++)
+#pragma unroll
+          for (int ct = 0; ct < CT; ct++) acc[rt][ct] = mfma16x16x4(a[u][rt], b[ct], acc[rt][ct]);
+      }
+    }
+    if (c + 1 < nchunk) {
+      fetch_a(c + 1);
+      commit_s(c + 1);
+    }
+    __syncthreads();
+  }
+  if (work) store_forward_small<T, RT, CT, MIR>(coeffs, p, w, b0, lane, acc);
+}
+
+template <class T, int RTMAX, int CT, int MIR>
+__global__ __launch_bounds__(MID_THREADS) void beta_forward_mid_kernel(const cpx<T>* __restrict__ S,
+                                                                       cpx<T>* __restrict__ coeffs, BetaParams<T> p,
+                                                                       int pos_end) {
+  typedef MidShape<T, RTMAX, CT, MIR> MS;
+  __shared__ __align__(16) T lds[2 * MIR * MS::HALF];
+  const int ntl = (pos_end - p.tile0 * PT + PT - 1) / PT;
+  const TileSlot sl = contraction_slot(blockIdx.x, ntl, (p.batch + MS::BT - 1) / MS::BT);
+  if (!sl.valid) return;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int tile = p.tile0 + sl.tile, b0 = sl.bt * MS::BT;
+  SmallPairs<T, MIR> w(p, tile * PT + wave);
+  if (tile * PT + wave >= pos_end) w.L = 0;  // the second half of a self-mirror tile
+  // row tiles of the workgroup's longest pair: one branch for all its waves
+  // (barriers inside)
+  int rt = 1;
+  if constexpr (RTMAX > 1) {
+    int L = 0;
+    for (int i = 0; i < PT; i++) L = max(L, p.pairs[tile * PT + i].L);
+    rt = (L + 15) / 16;
+  }
+  if constexpr (RTMAX >= 4) {
+    if (rt >= 4) return beta_forward_mid_body<T, RTMAX, 4, CT, MIR>(S, coeffs, p, w, tile, b0, lds, wave, lane);
+    if (rt == 3) return beta_forward_mid_body<T, RTMAX, 3, CT, MIR>(S, coeffs, p, w, tile, b0, lds, wave, lane);
+  }
+  if constexpr (RTMAX >= 2)
+    if (rt == 2) return beta_forward_mid_body<T, RTMAX, 2, CT, MIR>(S, coeffs, p, w, tile, b0, lds, wave, lane);
+  beta_forward_mid_body<T, RTMAX, 1, CT, MIR>(S, coeffs, p, w, tile, b0, lds, wave, lane);
+}
+
+// Inverse / adjoint: S'_k(m, n)[b] = sum_l s_l d^l(beta_k) fhat(l)_{mn}[b].
+// One workgroup of 16 waves per pair tile (and its mirror tile) and range of
+// 16-node blocks; a wave's scaled coefficients are its B operands, the
+// inverse-layout table its A operands.  A block's rows are gathered in LDS
+// and written as whole PT-pair rows of S.
+constexpr int SMALL_INV_THREADS = 64 * PT;
+
+template <class T, int BT>
+struct SmallStage {
+  static constexpr int PB = 2 * PT + 2, NRS = BT * PB + 4;
+};
+// two stage buffers (one barrier per block) where two workgroups per CU keep them
+template <class T, int BT, int MIR>
+constexpr int small_stages() { return 2 * MIR * 16 * SmallStage<T, BT>::NRS * (int)sizeof(T) <= 80 * 1024 ? 2 : 1; }
+
+template <class T, int LQ, int CT, int MIR>
+__global__ __launch_bounds__(SMALL_INV_THREADS) void beta_inverse_small_kernel(const cpx<T>* __restrict__ coeffs,
+                                                                               cpx<T>* __restrict__ S, BetaParams<T> p,
+                                                                               int ntl, int blocks) {
+  typedef typename acc4<T>::type accT;
+  typedef SmallCols<MIR, CT> Cols;
+  constexpr int BT = Cols::BT;
+  typedef SmallStage<T, BT> ST;
+  constexpr int NST = small_stages<T, BT, MIR>();
+  __shared__ __align__(16) T stages[NST][MIR * 16 * ST::NRS];
+  const int N = p.N, NB = (N + 15) / 16, nsplit = (NB + blocks - 1) / blocks;
+  const int nbt = (p.batch + BT - 1) / BT;
+  const TileSlot sl = contraction_slot(blockIdx.x, ntl, nsplit * nbt);
+  if (!sl.valid) return;
+  const int tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int lrow = lane & 15, lk = lane >> 4;
+  const int tile = p.tile0 + sl.tile, b0 = sl.bt / nsplit * BT;
+  const int kb0 = sl.bt % nsplit * blocks, kb1 = min(NB, kb0 + blocks);
+  const int nb = min(BT, p.batch - b0);
+  const SmallPairs<T, MIR> w(p, tile * PT + wave);
+  const int L = w.L, G = (L + 3) / 4;
+
+  const T* ta = p.tabi + w.itab + (long long)kb0 * G * 64 + lane;
+  T av[LQ];
+  auto fetch = [&]() {
+#pragma unroll
+    for (int s = 0; s < LQ; s++) {
+      av[s] = T(0);
+      if (s < G) av[s] = ta[64 * s];  // wave-uniform branch
+    }
+    ta += (long long)G * 64;
+  };
+  fetch();  // in flight while the coefficients are gathered
+
+  T bop[LQ][CT];
+#pragma unroll
+  for (int ct = 0; ct < CT; ct++) {
+    const int cc = ct * 16 + lrow, sig = Cols::sig(cc);
+    const auto q = w.pick(Cols::mir(cc));
+    const T* c = reinterpret_cast<const T*>(coeffs + coef_offset(p.coff, b0 + min(sig, nb - 1), p.ncoef)) + (cc & 1);
+    const T sg = ((((q.tm - q.tn) / 2) & 1) ? T(-1) : T(1)) * ((cc & 1) ? T(-1) : T(1));
+#pragma unroll
+    for (int s = 0; s < LQ; s++) {
+      bop[s][ct] = T(0);
+      if (s >= G) continue;
+      const int j = 4 * s + lk, tl = q.tl0 + 2 * j;
+      const bool ok = j < q.L && sig < nb;
+      T v = c[ok ? 2 * coef_index_of(p.so3, tl, q.tm, q.tn) : 0];
+      if (MIR == 1 && p.real)  // Hermitian part: (c_{mn} + (-1)^{m-n} conj(c_{-m,-n})) / 2
+        v = T(0.5) * (v + sg * c[ok ? 2 * coef_index_of(p.so3, tl, -q.tm, -q.tn) : 0]);
+      // (2l+1) or 1, times the sign of a mirror column of a stored table
+      const T sc = (p.scale_mode == 0 ? T(tl + 1) : T(1)) * (p.table_signs && q.tsign < 0 ? T(-1) : T(1));
+      bop[s][ct] = ok ? v * sc : T(0);
+    }
+  }
+
+  for (int kb = kb0; kb < kb1; kb++) {
+    accT acc[CT];
+#pragma unroll
+    for (int ct = 0; ct < CT; ct++)
+#pragma unroll
+      for (int r = 0; r < 4; r++) acc[ct][r] = T(0);
+#pragma unroll
+    for (int s = 0; s < LQ; s++)
+      if (s < G)
+#pragma unroll
+        for (int ct = 0; ct < CT; ct++) acc[ct] = mfma16x16x4(av[s], bop[s][ct], acc[ct]);
+    if (kb + 1 < kb1) fetch();  // next block's values, in flight during the stores
+    T* stage = stages[NST == 2 ? kb & 1 : 0];
+    if (NST == 1 && kb > kb0) __syncthreads();  // the previous block's rows are read
+#pragma unroll
+    for (int ct = 0; ct < CT; ct++) {
+      const int cc = ct * 16 + lrow, mir = MIR == 2 ? Cols::mir(cc) : 0;
+      T* d = stage + mir * 16 * ST::NRS + Cols::sig(cc) * ST::PB + 2 * (mir ? PT - 1 - wave : wave) + (cc & 1);
+#pragma unroll
+      for (int r = 0; r < 4; r++) d[acc_row<T>(lane, r) * ST::NRS] = acc[ct][r];
+    }
+    __syncthreads();
+    // rows (node, signal) of PT pairs, 16 bytes per store
+    constexpr int VC = 16 / (int)sizeof(cpx<T>), VPR = PT / VC;
+    typedef T vec16 __attribute__((ext_vector_type(16 / sizeof(T))));
+    const int mirs = MIR == 2 && p.ntiles - 1 - tile == tile ? 1 : MIR;  // a self-mirror tile once
+    for (int v = tid; v < mirs * 16 * BT * VPR; v += SMALL_INV_THREADS) {
+      const int pv = v % VPR, bb = v / VPR % BT, kk = v / (VPR * BT) % 16, mir = v / (VPR * BT * 16);
+      const int k = 16 * kb + kk;
+      if (k >= N || bb >= nb) continue;
+      const T* src = stage + (mir * 16 + kk) * ST::NRS + bb * ST::PB + 2 * pv * VC;
+      vec16 x;
+#pragma unroll
+      for (int e = 0; e < 2 * VC; e++) x[e] = src[e];
+      const int t = mir ? p.ntiles - 1 - tile : tile;
+      *reinterpret_cast<vec16*>(S + (((size_t)t * N + k) * p.batch + b0 + bb) * PT + pv * VC) = x;
+    }
+  }
+}
+
+// pairs of a wave: a pair and its mirror where the plan's list is
+// point-symmetric and every pair carries spectra
+template <class T>
+static bool small_mirrored(const BetaParams<T>& p) { return p.sym && !p.real; }
+
+// Up to 8 signals; above, the tile kernels' staged tables serve enough columns
+// (B = 64 FP32, 12 signals: forward 46 us against 72, inverse 34 against 58).
+// The inverse up to 8 degrees (B <= 16) stays with the tile kernel, as fast and
+// smaller.  Forward / inverse, us, tile kernel -> these: B = 64 FP32, 1 signal
+// 42 -> 14 / 27 -> 13, 8 signals 45 -> 31 / 31 -> 25; FP64, 1 signal 57 -> 15 /
+// 53 -> 19; B = 36 FP32, 1 signal 16 -> 7 / 12 -> 7; B = 128 FP64, 1 signal
+// 795 -> 241 / 745 -> 263 (the table alone takes 133 at the copy rate).
+constexpr int SMALL_BATCH = 8;
+template <class T>
+bool beta_small_forward(const BetaParams<T>& p) { return p.batch <= SMALL_BATCH; }
+template <class T>
+bool beta_small_inverse(const BetaParams<T>& p) { return p.batch <= SMALL_BATCH && p.B > 16; }
+
+// Forward with the spectra through LDS: where the lines of S that the
+// LDS-free kernel reads piecemeal outweigh the barriers, i.e. by signals times
+// tiles, and only with enough tiles to give most CUs a workgroup.  LDS-free ->
+// through LDS, us: FP32 B = 128, 1 signal 144 -> 123, 2 signals 202 -> 132; B = 96,
+// 1 signal 41 -> 46, 4 signals 76 -> 53; B = 64, 2 signals 15.1 -> 15.4, 8 signals
+// 42 -> 31; B = 48 (142 tiles), 4 signals 10 -> 12.  FP64, whose products take
+// twice as long and whose chunks hold half the nodes, B = 64, 2 signals
+// 20 -> 23, 4 signals 28 -> 26; B = 128, 1 signal 241 -> 251, 2 signals 302 -> 266.
+template <class T>
+static bool small_through_lds(const BetaParams<T>& p) {
+  const long long units = small_mirrored(p) ? (p.ntiles + 1) / 2 : p.ntiles - p.tile0;
+  return 4 * units >= 3LL * device_cus() && (2LL * p.batch - 1) * units >= (sizeof(T) == 4 ? 750 : 1750);
+}
+
+template <class T, int CT, int MIR>
+static hipError_t launch_forward_mid(const BetaParams<T>& p, const cpx<T>* S, cpx<T>* coeffs, hipStream_t s) {
+  constexpr int BT = SmallCols<MIR, CT>::BT;
+  const int pos_end = MIR == 2 ? p.ntiles * PT / 2 : p.ntiles * PT;
+  const int ntl = (pos_end - p.tile0 * PT + PT - 1) / PT, nbt = (p.batch + BT - 1) / BT;
+  const dim3 grid(contraction_grid(ntl, nbt)), block(MID_THREADS);
+  switch (beta_rtmax(p.B)) {
+    case 1: hipLaunchKernelGGL((beta_forward_mid_kernel<T, 1, CT, MIR>), grid, block, 0, s, S, coeffs, p, pos_end); break;
+    case 2: hipLaunchKernelGGL((beta_forward_mid_kernel<T, 2, CT, MIR>), grid, block, 0, s, S, coeffs, p, pos_end); break;
+    default: hipLaunchKernelGGL((beta_forward_mid_kernel<T, 4, CT, MIR>), grid, block, 0, s, S, coeffs, p, pos_end); break;
+  }
+  return hipGetLastError();
+}
+
+template <class T, int CT, int MIR>
+static hipError_t launch_forward_small(const BetaParams<T>& p, const cpx<T>* S, cpx<T>* coeffs, hipStream_t s) {
+  constexpr int BT = SmallCols<MIR, CT>::BT;
+  const int pos_end = MIR == 2 ? p.ntiles * PT / 2 : p.ntiles * PT;
+  const int ntl = (pos_end - p.tile0 * PT + PT - 1) / PT, nbt = (p.batch + BT - 1) / BT;
+  const dim3 grid(contraction_grid(ntl, PT / SMALL_FWD_WAVES * nbt)), block(64 * SMALL_FWD_WAVES);
+  switch (beta_rtmax(p.B)) {
+    case 1: hipLaunchKernelGGL((beta_forward_small_kernel<T, 1, CT, MIR>), grid, block, 0, s, S, coeffs, p, pos_end); break;
+    case 2: hipLaunchKernelGGL((beta_forward_small_kernel<T, 2, CT, MIR>), grid, block, 0, s, S, coeffs, p, pos_end); break;
+    default: hipLaunchKernelGGL((beta_forward_small_kernel<T, 4, CT, MIR>), grid, block, 0, s, S, coeffs, p, pos_end); break;
+  }
+  return hipGetLastError();
+}
+
+// products side by side that the inverse has registers for (16 waves per
+// workgroup: at most 128 per lane)
+template <class T, int LQ, int CT>
+constexpr int small_inverse_ct() {
+  constexpr int most = sizeof(T) == 4 ? (LQ == 16 ? 2 : 4) : (LQ == 16 ? 1 : (LQ == 8 ? 2 : 4));
+  return CT < most ? CT : most;
+}
+
+template <class T, int LQ, int CT, int MIR>
+static hipError_t launch_inverse_small_lq(const BetaParams<T>& p, const cpx<T>* coeffs, cpx<T>* S, hipStream_t s) {
+  constexpr int BT = SmallCols<MIR, CT>::BT;
+  const int ntl = MIR == 2 ? (p.ntiles + 1) / 2 : p.ntiles - p.tile0, nbt = (p.batch + BT - 1) / BT;
+  const int NB = (p.N + 15) / 16;
+  // node blocks per workgroup: the fewest block times, counting the coefficient
+  // gather at a workgroup's start as two, with two workgroups per CU at a time
+  const long long slots = 2LL * device_cus(), have = (long long)ntl * nbt;
+  int blocks = NB;
+  long long best = 0;
+  for (int b = NB; b >= 1; b--) {
+    const long long nsplit = (NB + b - 1) / b, cost = (have * nsplit + slots - 1) / slots * (b + 2);
+    if (b == NB || cost < best) {
+      best = cost;
+      blocks = b;
+    }
+  }
+  const dim3 grid(contraction_grid(ntl, (NB + blocks - 1) / blocks * nbt)), block(SMALL_INV_THREADS);
+  hipLaunchKernelGGL((beta_inverse_small_kernel<T, LQ, CT, MIR>), grid, block, 0, s, coeffs, S, p, ntl, blocks);
+  return hipGetLastError();
+}
+
+template <class T, int CT, int MIR>
+static hipError_t launch_inverse_small(const BetaParams<T>& p, const cpx<T>* coeffs, cpx<T>* S, hipStream_t s) {
+  switch (beta_lq(p.B)) {
+    case 2: return launch_inverse_small_lq<T, 2, small_inverse_ct<T, 2, CT>(), MIR>(p, coeffs, S, s);
+    case 4: return launch_inverse_small_lq<T, 4, small_inverse_ct<T, 4, CT>(), MIR>(p, coeffs, S, s);
+    case 8: return launch_inverse_small_lq<T, 8, small_inverse_ct<T, 8, CT>(), MIR>(p, coeffs, S, s);
+    default: return launch_inverse_small_lq<T, 16, small_inverse_ct<T, 16, CT>(), MIR>(p, coeffs, S, s);
+  }
+}
+
+// products per wave side by side: the narrowest that hold the batch
+template <class T>
+hipError_t launch_beta_forward_small(const BetaParams<T>& p, const cpx<T>* S, cpx<T>* coeffs, hipStream_t s) {
+  const bool mid = small_through_lds(p);
+  if (!small_mirrored(p))
+    return mid ? launch_forward_mid<T, 1, 1>(p, S, coeffs, s) : launch_forward_small<T, 1, 1>(p, S, coeffs, s);
+  if (p.batch <= 4)
+    return mid ? launch_forward_mid<T, 1, 2>(p, S, coeffs, s) : launch_forward_small<T, 1, 2>(p, S, coeffs, s);
+  return mid ? launch_forward_mid<T, 2, 2>(p, S, coeffs, s) : launch_forward_small<T, 2, 2>(p, S, coeffs, s);
+}
+template <class T>
+hipError_t launch_beta_inverse_small(const BetaParams<T>& p, const cpx<T>* coeffs, cpx<T>* S, hipStream_t s) {
+  if (!small_mirrored(p)) return launch_inverse_small<T, 1, 1>(p, coeffs, S, s);
+  if (p.batch <= 4) return launch_inverse_small<T, 1, 2>(p, coeffs, S, s);
+  return launch_inverse_small<T, 2, 2>(p, coeffs, S, s);
+}
+
+template bool beta_small_forward<float>(const BetaParams<float>&);
+template bool beta_small_forward<double>(const BetaParams<double>&);
+template bool beta_small_inverse<float>(const BetaParams<float>&);
+template bool beta_small_inverse<double>(const BetaParams<double>&);
+template hipError_t launch_beta_forward_small<float>(const BetaParams<float>&, const cpx<float>*, cpx<float>*,
+                                                     hipStream_t);
+template hipError_t launch_beta_forward_small<double>(const BetaParams<double>&, const cpx<double>*, cpx<double>*,
+                                                      hipStream_t);
+template hipError_t launch_beta_inverse_small<float>(const BetaParams<float>&, const cpx<float>*, cpx<float>*,
+                                                     hipStream_t);
+template hipError_t launch_beta_inverse_small<double>(const BetaParams<double>&, const cpx<double>*, cpx<double>*,
+                                                      hipStream_t);
+
+}  // namespace su2

@@ -540,11 +540,11 @@ su2_status_t build_plan(su2_plan_s* pl) {
   // shifted-recurrence contraction use them (a few MB)
   if ((e = upload_otf_scalars(pl, beta)) != hipSuccess) return hip_fail(e);
   if (!pl->otf) {
-    // tables are padded by 64 bytes of zeros: the contraction kernels read
-    // whole 16-byte vectors, and up to 3 elements past a pair's row segment
-    // (multiplied by zero operands)
-    if ((e = pl->alloc((void**)&pl->d_tab64, sizeof(double) * (size_t)tab + 64)) != hipSuccess) return hip_fail(e);
-    if ((e = hipMemset(pl->d_tab64 + tab, 0, 64)) != hipSuccess) return hip_fail(e);
+    // tables are padded by 16 zeros: the contraction kernels read whole
+    // 16-byte vectors, and up to 15 elements past a pair's row segment
+    // (multiplied by zero operands, or in result rows that are dropped)
+    if ((e = pl->alloc((void**)&pl->d_tab64, sizeof(double) * ((size_t)tab + 16))) != hipSuccess) return hip_fail(e);
+    if ((e = hipMemset(pl->d_tab64 + tab, 0, 16 * sizeof(double))) != hipSuccess) return hip_fail(e);
     if ((e = launch_dtable(B, N, pl->P_pad, pl->d_pairs, d_beta, pl->d_tab64, 0)) != hipSuccess) return hip_fail(e);
     // the inverse-layout copy read by the inverse and adjoint contractions
     if (pl->dtype == SU2_C128) {

@@ -199,6 +199,7 @@ struct BetaParams {
   int tile0;                // first pair tile launched (grid x = ntiles - tile0)
   int so3;                  // SO(3) plan: integer-l coefficient layout
   int table_signs;          // stored tables with mirror columns: multiply read values by PairInfo::tsign
+  int sym;                  // point-symmetric pair list: position i mirrors P_pad - 1 - i and shares its table column
   int paired;               // mirror tiles t, ntiles - 1 - t share a table block: the forward launches them side by side
 };
 
@@ -299,6 +300,16 @@ template <class T>
 hipError_t launch_beta_forward(const BetaParams<T>& p, const cpx<T>* S, cpx<T>* coeffs, hipStream_t s);
 template <class T>
 hipError_t launch_beta_inverse(const BetaParams<T>& p, const cpx<T>* coeffs, cpx<T>* S, hipStream_t s);
+// small batches (su2fft_beta_small.hip): whether the streaming kernels take a
+// call, and their launches
+template <class T>
+bool beta_small_forward(const BetaParams<T>& p);
+template <class T>
+bool beta_small_inverse(const BetaParams<T>& p);
+template <class T>
+hipError_t launch_beta_forward_small(const BetaParams<T>& p, const cpx<T>* S, cpx<T>* coeffs, hipStream_t s);
+template <class T>
+hipError_t launch_beta_inverse_small(const BetaParams<T>& p, const cpx<T>* coeffs, cpx<T>* S, hipStream_t s);
 template <class T>
 hipError_t launch_beta_forward_otf(const OtfParams<T>& p, const cpx<T>* S, cpx<T>* coeffs, hipStream_t s);
 template <class T>

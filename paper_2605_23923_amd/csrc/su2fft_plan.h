@@ -174,6 +174,7 @@ BetaParams<T> beta_params(const su2_plan_s* pl, const T* tab, int scale_mode) {
   b.tile0 = half ? pl->rbeg[0] / PT : 0;
   b.so3 = pl->so3 ? 1 : 0;
   b.table_signs = pl->sym ? 1 : 0;
+  b.sym = pl->sym ? 1 : 0;
   // (mixed-radix plans keep the natural order: with few tiles the mirror
   // pairs spread unevenly over the XCDs, B = 24, 151 signals 26.7 against
   // 19.6 us, and B = 48 and 96 gained nothing either)
