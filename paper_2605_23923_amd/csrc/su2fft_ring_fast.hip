@@ -837,7 +837,9 @@ static hipError_t launch_fast(bool forward, bool real, const FastRingParams<T>& 
     // only: the real variant of the paired kernel rounds some values
     // differently (last bits) from the single-ring body that mixed plans run,
     // and real plans keep the single-ring kernel so that both agree bit for bit.
-    if (!forward && !real) {
+    // Up to 2 signals the pairs would fill at most half of the 256 CUs: one ring
+    // per workgroup there (1 signal 35 -> 23 us).
+    if (!forward && !real && p.batch > 2) {
       const void* kern = (const void*)ring_inverse_fast_pair<T, false>;
       hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)R::SMEM);
       if (e != hipSuccess) return e;
