@@ -7,21 +7,23 @@
 // columns empty, and one staged chunk per workgroup keeps too few bytes in
 // flight.  Here a wave owns one pair (m, n) together with its mirror
 // (-m, -n), which uses the same table column up to sign: the columns of one
-// 16-wide product are 2 pairs x 4 signals x (re, im) (CT products side by side
-// for more signals), every table value is read once per launch, by coalesced
-// loads that go directly into operand registers, many of them in flight, and
-// the forward has no LDS and no barrier at all.  Plans without the symmetric
+// 16-wide product are 2 pairs x 4 signals x (re, im), every table value is
+// read once per 4 signals, by coalesced loads that go directly into operand
+// registers, many of them in flight, and the forward has no LDS and no barrier
+// at all.  More signals take more waves, which share the table through L2
+// (two products side by side per wave measured slower: B = 48 FP64, 12 signals
+// inverse 37 against 22 us).  Plans without the symmetric
 // pair list, and half-spectrum real plans (whose mirrors carry no spectra),
-// take one pair per wave and twice the signals per product.
+// take one pair per wave and 8 signals per product.
 #include "su2fft_mfma.h"
 
 namespace su2 {
 
 // column cc of a wave's products: which of its MIR pairs, which signal of the
 // tile's BT, and re or im
-template <int MIR, int CT>
+template <int MIR>
 struct SmallCols {
-  static constexpr int BT = 8 * CT / MIR;
+  static constexpr int BT = 8 / MIR;
   __device__ static __forceinline__ int mir(int cc) { return cc / (2 * BT); }
   __device__ static __forceinline__ int sig(int cc) { return cc % (2 * BT) / 2; }
 };
@@ -68,41 +70,37 @@ struct SmallPairs {
 constexpr int SMALL_FWD_WAVES = 4;  // waves (pairs) per workgroup: a quarter of a tile
 
 // a wave's sums out to the coefficient vectors
-template <class T, int RT, int CT, int MIR>
+template <class T, int RT, int MIR>
 __device__ __forceinline__ void store_forward_small(cpx<T>* __restrict__ coeffs, const BetaParams<T>& p,
                                                     const SmallPairs<T, MIR>& w, int b0, int lane,
-                                                    const typename acc4<T>::type (&acc)[RT][CT]) {
-  typedef SmallCols<MIR, CT> Cols;
-  const int lrow = lane & 15;
+                                                    const typename acc4<T>::type (&acc)[RT]) {
+  typedef SmallCols<MIR> Cols;
+  const int col = lane & 15, b = b0 + Cols::sig(col);
+  const auto q = w.pick(Cols::mir(col));
+  if (b >= p.batch) return;
+  const T ts = p.table_signs && q.tsign < 0 ? T(-1) : T(1);
+  T* out = reinterpret_cast<T*>(coeffs + coef_offset(p.coff, b, p.ncoef)) + (col & 1);
+  // half-spectrum real plans also write the mirror (-1)^{m-n} conj(fhat) at (-m, -n)
+  const bool mirror = MIR == 1 && p.real && (q.tm != 0 || q.tn != 0);
+  const T sg = ((((q.tm - q.tn) / 2) & 1) ? T(-1) : T(1)) * ((col & 1) ? T(-1) : T(1));
 #pragma unroll
-  for (int ct = 0; ct < CT; ct++) {
-    const int cc = ct * 16 + lrow, b = b0 + Cols::sig(cc);
-    const auto q = w.pick(Cols::mir(cc));
-    if (b >= p.batch) continue;
-    const T ts = p.table_signs && q.tsign < 0 ? T(-1) : T(1);
-    T* out = reinterpret_cast<T*>(coeffs + coef_offset(p.coff, b, p.ncoef)) + (cc & 1);
-    // half-spectrum real plans also write the mirror (-1)^{m-n} conj(fhat) at (-m, -n)
-    const bool mirror = MIR == 1 && p.real && (q.tm != 0 || q.tn != 0);
-    const T sg = ((((q.tm - q.tn) / 2) & 1) ? T(-1) : T(1)) * ((cc & 1) ? T(-1) : T(1));
+  for (int rt = 0; rt < RT; rt++)
 #pragma unroll
-    for (int rt = 0; rt < RT; rt++)
-#pragma unroll
-      for (int r = 0; r < 4; r++) {
-        const int j = RT * acc_row<T>(lane, r) + rt;
-        if (j >= q.L) continue;
-        const T v = ts * acc[rt][ct][r];
-        out[2 * coef_index_of(p.so3, q.tl0 + 2 * j, q.tm, q.tn)] = v;
-        if (mirror) out[2 * coef_index_of(p.so3, q.tl0 + 2 * j, -q.tm, -q.tn)] = sg * v;
-      }
-  }
+    for (int r = 0; r < 4; r++) {
+      const int j = RT * acc_row<T>(lane, r) + rt;
+      if (j >= q.L) continue;
+      const T v = ts * acc[rt][r];
+      out[2 * coef_index_of(p.so3, q.tl0 + 2 * j, q.tm, q.tn)] = v;
+      if (mirror) out[2 * coef_index_of(p.so3, q.tl0 + 2 * j, -q.tm, -q.tn)] = sg * v;
+    }
 }
 
-template <class T, int RT, int CT, int MIR>
+template <class T, int RT, int MIR>
 __device__ __forceinline__ void beta_forward_small_pair(const cpx<T>* __restrict__ S, cpx<T>* __restrict__ coeffs,
                                                         const BetaParams<T>& p, const SmallPairs<T, MIR>& w, int b0,
                                                         int lane) {
   typedef typename acc4<T>::type accT;
-  typedef SmallCols<MIR, CT> Cols;
+  typedef SmallCols<MIR> Cols;
   // RT adjacent table values, at any element's alignment
   typedef T rowv __attribute__((ext_vector_type(RT), aligned(sizeof(T))));
   constexpr int KU = RT == 1 ? (sizeof(T) == 4 ? 16 : 8) : (RT == 2 ? 8 : 4);
@@ -111,43 +109,31 @@ __device__ __forceinline__ void beta_forward_small_pair(const cpx<T>* __restrict
   // pair's (or the padding after the table) and are dropped; signals past the
   // batch read the last one and are dropped likewise.
   const T* ta = p.tab + w.tab + (long long)lk * w.lsum + RT * lrow;
-  const T* tb[CT];
-#pragma unroll
-  for (int ct = 0; ct < CT; ct++) {
-    const int cc = ct * 16 + lrow, pos = MIR == 2 && Cols::mir(cc) ? w.pos1 : w.pos0;
-    const int b = min(b0 + Cols::sig(cc), p.batch - 1);
-    tb[ct] = reinterpret_cast<const T*>(S + (((size_t)(pos / PT) * N + lk) * p.batch + b) * PT + pos % PT) + (cc & 1);
-  }
+  const int pos = MIR == 2 && Cols::mir(lrow) ? w.pos1 : w.pos0, bs = min(b0 + Cols::sig(lrow), p.batch - 1);
+  const T* tb = reinterpret_cast<const T*>(S + (((size_t)(pos / PT) * N + lk) * p.batch + bs) * PT + pos % PT) + (lrow & 1);
   const long long sa = 4LL * w.lsum, sb = 8LL * p.batch * PT;
 
-  accT acc[RT][CT];
+  accT acc[RT];
 #pragma unroll
   for (int rt = 0; rt < RT; rt++)
 #pragma unroll
-    for (int ct = 0; ct < CT; ct++)
-#pragma unroll
-      for (int r = 0; r < 4; r++) acc[rt][ct][r] = T(0);
+    for (int r = 0; r < 4; r++) acc[rt][r] = T(0);
 
-  auto load = [&](rowv& a, T (&b)[CT]) {
+  auto load = [&](rowv& a, T& b) {
     a = *reinterpret_cast<const rowv*>(ta);
     ta += sa;
-#pragma unroll
-    for (int ct = 0; ct < CT; ct++) {
-      b[ct] = *tb[ct];
-      tb[ct] += sb;
-    }
+    b = *tb;
+    tb += sb;
   };
-  auto products = [&](const rowv& a, const T (&b)[CT]) {
+  auto products = [&](const rowv& a, const T b) {
 #pragma unroll
-    for (int rt = 0; rt < RT; rt++)
-#pragma unroll
-      for (int ct = 0; ct < CT; ct++) acc[rt][ct] = mfma16x16x4(a[rt], b[ct], acc[rt][ct]);
+    for (int rt = 0; rt < RT; rt++) acc[rt] = mfma16x16x4(a[rt], b, acc[rt]);
   };
   const int ng = N / 4;  // whole groups of 4 nodes
   int g = 0;
   for (; g + KU <= ng; g += KU) {
     rowv a[KU];
-    T b[KU][CT];
+    T b[KU];
 #pragma unroll
     for (int u = 0; u < KU; u++) load(a[u], b[u]);
 #pragma unroll
@@ -156,7 +142,7 @@ __device__ __forceinline__ void beta_forward_small_pair(const cpx<T>* __restrict
   if constexpr (KU > 4)
     for (; g + 4 <= ng; g += 4) {
       rowv a[4];
-      T b[4][CT];
+      T b[4];
 #pragma unroll
       for (int u = 0; u < 4; u++) load(a[u], b[u]);
 #pragma unroll
@@ -164,30 +150,27 @@ __device__ __forceinline__ void beta_forward_small_pair(const cpx<T>* __restrict
     }
   for (; g < ng; g++) {
     rowv a;
-    T b[CT];
+    T b;
     load(a, b);
     products(a, b);
   }
   if (N % 4 != 0) {  // the last N mod 4 nodes, zeros past them
     const bool in = 4 * ng + lk < N;
     rowv a;
-    T b[CT];
 #pragma unroll
     for (int rt = 0; rt < RT; rt++) a[rt] = in ? ta[rt] : T(0);
-#pragma unroll
-    for (int ct = 0; ct < CT; ct++) b[ct] = in ? *tb[ct] : T(0);
-    products(a, b);
+    products(a, in ? *tb : T(0));
   }
 
-  store_forward_small<T, RT, CT, MIR>(coeffs, p, w, b0, lane, acc);
+  store_forward_small<T, RT, MIR>(coeffs, p, w, b0, lane, acc);
 }
 
 // RTMAX: row tiles of the plan's longest pairs (beta_rtmax)
-template <class T, int RTMAX, int CT, int MIR>
+template <class T, int RTMAX, int MIR>
 __global__ __launch_bounds__(64 * SMALL_FWD_WAVES) void beta_forward_small_kernel(const cpx<T>* __restrict__ S,
                                                                                   cpx<T>* __restrict__ coeffs,
                                                                                   BetaParams<T> p, int pos_end) {
-  constexpr int BT = SmallCols<MIR, CT>::BT, QT = PT / SMALL_FWD_WAVES;
+  constexpr int BT = SmallCols<MIR>::BT, QT = PT / SMALL_FWD_WAVES;
   const int nbt = (p.batch + BT - 1) / BT;
   const int ntl = (pos_end - p.tile0 * PT + PT - 1) / PT;
   const TileSlot sl = contraction_slot(blockIdx.x, ntl, QT * nbt);
@@ -199,12 +182,12 @@ __global__ __launch_bounds__(64 * SMALL_FWD_WAVES) void beta_forward_small_kerne
   if (w.L == 0) return;
   const int rt = (w.L + 15) / 16;  // uniform
   if constexpr (RTMAX >= 4) {
-    if (rt == 4) return beta_forward_small_pair<T, 4, CT, MIR>(S, coeffs, p, w, b0, lane);
-    if (rt == 3) return beta_forward_small_pair<T, 3, CT, MIR>(S, coeffs, p, w, b0, lane);
+    if (rt == 4) return beta_forward_small_pair<T, 4, MIR>(S, coeffs, p, w, b0, lane);
+    if (rt == 3) return beta_forward_small_pair<T, 3, MIR>(S, coeffs, p, w, b0, lane);
   }
   if constexpr (RTMAX >= 2)
-    if (rt == 2) return beta_forward_small_pair<T, 2, CT, MIR>(S, coeffs, p, w, b0, lane);
-  beta_forward_small_pair<T, 1, CT, MIR>(S, coeffs, p, w, b0, lane);
+    if (rt == 2) return beta_forward_small_pair<T, 2, MIR>(S, coeffs, p, w, b0, lane);
+  beta_forward_small_pair<T, 1, MIR>(S, coeffs, p, w, b0, lane);
 }
 
 // Forward with the spectra through LDS, from a few signals on: a wave that
@@ -215,25 +198,25 @@ __global__ __launch_bounds__(64 * SMALL_FWD_WAVES) void beta_forward_small_kerne
 // to registers.
 constexpr int MID_THREADS = 64 * PT;
 
-template <class T, int RTMAX, int CT, int MIR>
+template <class T, int RTMAX, int MIR>
 struct MidShape {
-  static constexpr int BT = SmallCols<MIR, CT>::BT;
+  static constexpr int BT = SmallCols<MIR>::BT;
   // 70 KB for the two buffers, two workgroups per CU (half of it where the
   // operands of 64 degrees need the registers)
-  static constexpr int KG = sizeof(T) == 4 ? (RTMAX == 4 && CT == 1 ? 4 : 8 / CT) : 4 / CT;
+  static constexpr int KG = sizeof(T) == 4 && RTMAX < 4 ? 8 : 4;
   static constexpr int KN = 4 * KG;
   static constexpr int PB = 2 * PT + 2, HALF = KN * BT * PB + 2;  // one of the MIR tiles' rows
   static constexpr int VC = 16 / (int)sizeof(cpx<T>), VPR = PT / VC;  // 16-byte vectors per row
   static constexpr int NV = MIR * KN * BT * VPR, VPT = (NV + MID_THREADS - 1) / MID_THREADS;
 };
 
-template <class T, int RTMAX, int RT, int CT, int MIR>
+template <class T, int RTMAX, int RT, int MIR>
 __device__ __forceinline__ void beta_forward_mid_body(const cpx<T>* __restrict__ S, cpx<T>* __restrict__ coeffs,
                                                       const BetaParams<T>& p, const SmallPairs<T, MIR>& w, int tile,
                                                       int b0, T* lds, int wave, int lane) {
   typedef typename acc4<T>::type accT;
-  typedef SmallCols<MIR, CT> Cols;
-  typedef MidShape<T, RTMAX, CT, MIR> MS;
+  typedef SmallCols<MIR> Cols;
+  typedef MidShape<T, RTMAX, MIR> MS;
   typedef T rowv __attribute__((ext_vector_type(RT), aligned(sizeof(T))));
   typedef T vec16 __attribute__((ext_vector_type(16 / sizeof(T))));
   constexpr int KG = MS::KG, KN = MS::KN, BT = MS::BT;
@@ -276,20 +259,14 @@ __device__ __forceinline__ void beta_forward_mid_body(const cpx<T>* __restrict__
       if (work && 4 * g + lk < N) a[u] = *reinterpret_cast<const rowv*>(ta + g * sa);
     }
   };
-  int bofs[CT];
-#pragma unroll
-  for (int ct = 0; ct < CT; ct++) {
-    const int cc = ct * 16 + lrow, mir = MIR == 2 ? Cols::mir(cc) : 0;
-    bofs[ct] = mir * MS::HALF + (lk * BT + Cols::sig(cc)) * MS::PB + 2 * (mir ? PT - 1 - wave : wave) + (cc & 1);
-  }
+  const int hm = MIR == 2 ? Cols::mir(lrow) : 0;
+  const int bofs = hm * MS::HALF + (lk * BT + Cols::sig(lrow)) * MS::PB + 2 * (hm ? PT - 1 - wave : wave) + (lrow & 1);
 
-  accT acc[RT][CT];
+  accT acc[RT];
 #pragma unroll
   for (int rt = 0; rt < RT; rt++)
 #pragma unroll
-    for (int ct = 0; ct < CT; ct++)
-#pragma unroll
-      for (int r = 0; r < 4; r++) acc[rt][ct][r] = T(0);
+    for (int r = 0; r < 4; r++) acc[rt][r] = T(0);
   fetch_s(0);
   fetch_a(0);
   commit_s(0);
@@ -301,13 +278,9 @@ __device__ __forceinline__ void beta_forward_mid_body(const cpx<T>* __restrict__
 #pragma unroll
       for (int u = 0; u < KG; u++) {
         if (c * KG + u >= ng) break;
-        T b[CT];
+        const T b = src[bofs + 4 * u * BT * MS::PB];
 #pragma unroll
-        for (int ct = 0; ct < CT; ct++) b[ct] = src[bofs[ct] + 4 * u * BT * MS::PB];
-#pragma unroll
-        for (int rt = 0; rt < RT; rt++)
-#pragma unroll
-          for (int ct = 0; ct < CT; ct++) acc[rt][ct] = mfma16x16x4(a[u][rt], b[ct], acc[rt][ct]);
+        for (int rt = 0; rt < RT; rt++) acc[rt] = mfma16x16x4(a[u][rt], b, acc[rt]);
       }
     }
     if (c + 1 < nchunk) {
@@ -316,14 +289,14 @@ __device__ __forceinline__ void beta_forward_mid_body(const cpx<T>* __restrict__
     }
     __syncthreads();
   }
-  if (work) store_forward_small<T, RT, CT, MIR>(coeffs, p, w, b0, lane, acc);
+  if (work) store_forward_small<T, RT, MIR>(coeffs, p, w, b0, lane, acc);
 }
 
-template <class T, int RTMAX, int CT, int MIR>
+template <class T, int RTMAX, int MIR>
 __global__ __launch_bounds__(MID_THREADS) void beta_forward_mid_kernel(const cpx<T>* __restrict__ S,
                                                                        cpx<T>* __restrict__ coeffs, BetaParams<T> p,
                                                                        int pos_end) {
-  typedef MidShape<T, RTMAX, CT, MIR> MS;
+  typedef MidShape<T, RTMAX, MIR> MS;
   __shared__ __align__(16) T lds[2 * MIR * MS::HALF];
   const int ntl = (pos_end - p.tile0 * PT + PT - 1) / PT;
   const TileSlot sl = contraction_slot(blockIdx.x, ntl, (p.batch + MS::BT - 1) / MS::BT);
@@ -341,12 +314,12 @@ __global__ __launch_bounds__(MID_THREADS) void beta_forward_mid_kernel(const cpx
     rt = (L + 15) / 16;
   }
   if constexpr (RTMAX >= 4) {
-    if (rt >= 4) return beta_forward_mid_body<T, RTMAX, 4, CT, MIR>(S, coeffs, p, w, tile, b0, lds, wave, lane);
-    if (rt == 3) return beta_forward_mid_body<T, RTMAX, 3, CT, MIR>(S, coeffs, p, w, tile, b0, lds, wave, lane);
+    if (rt >= 4) return beta_forward_mid_body<T, RTMAX, 4, MIR>(S, coeffs, p, w, tile, b0, lds, wave, lane);
+    if (rt == 3) return beta_forward_mid_body<T, RTMAX, 3, MIR>(S, coeffs, p, w, tile, b0, lds, wave, lane);
   }
   if constexpr (RTMAX >= 2)
-    if (rt == 2) return beta_forward_mid_body<T, RTMAX, 2, CT, MIR>(S, coeffs, p, w, tile, b0, lds, wave, lane);
-  beta_forward_mid_body<T, RTMAX, 1, CT, MIR>(S, coeffs, p, w, tile, b0, lds, wave, lane);
+    if (rt == 2) return beta_forward_mid_body<T, RTMAX, 2, MIR>(S, coeffs, p, w, tile, b0, lds, wave, lane);
+  beta_forward_mid_body<T, RTMAX, 1, MIR>(S, coeffs, p, w, tile, b0, lds, wave, lane);
 }
 
 // Inverse / adjoint: S'_k(m, n)[b] = sum_l s_l d^l(beta_k) fhat(l)_{mn}[b].
@@ -360,20 +333,16 @@ template <class T, int BT>
 struct SmallStage {
   static constexpr int PB = 2 * PT + 2, NRS = BT * PB + 4;
 };
-// two stage buffers (one barrier per block) where two workgroups per CU keep them
-template <class T, int BT, int MIR>
-constexpr int small_stages() { return 2 * MIR * 16 * SmallStage<T, BT>::NRS * (int)sizeof(T) <= 80 * 1024 ? 2 : 1; }
 
-template <class T, int LQ, int CT, int MIR>
+template <class T, int LQ, int MIR>
 __global__ __launch_bounds__(SMALL_INV_THREADS) void beta_inverse_small_kernel(const cpx<T>* __restrict__ coeffs,
                                                                                cpx<T>* __restrict__ S, BetaParams<T> p,
                                                                                int ntl, int blocks) {
   typedef typename acc4<T>::type accT;
-  typedef SmallCols<MIR, CT> Cols;
+  typedef SmallCols<MIR> Cols;
   constexpr int BT = Cols::BT;
   typedef SmallStage<T, BT> ST;
-  constexpr int NST = small_stages<T, BT, MIR>();
-  __shared__ __align__(16) T stages[NST][MIR * 16 * ST::NRS];
+  __shared__ __align__(16) T stages[2][MIR * 16 * ST::NRS];
   const int N = p.N, NB = (N + 15) / 16, nsplit = (NB + blocks - 1) / blocks;
   const int nbt = (p.batch + BT - 1) / BT;
   const TileSlot sl = contraction_slot(blockIdx.x, ntl, nsplit * nbt);
@@ -399,16 +368,15 @@ __global__ __launch_bounds__(SMALL_INV_THREADS) void beta_inverse_small_kernel(c
   };
   fetch();  // in flight while the coefficients are gathered
 
-  T bop[LQ][CT];
-#pragma unroll
-  for (int ct = 0; ct < CT; ct++) {
-    const int cc = ct * 16 + lrow, sig = Cols::sig(cc);
-    const auto q = w.pick(Cols::mir(cc));
-    const T* c = reinterpret_cast<const T*>(coeffs + coef_offset(p.coff, b0 + min(sig, nb - 1), p.ncoef)) + (cc & 1);
-    const T sg = ((((q.tm - q.tn) / 2) & 1) ? T(-1) : T(1)) * ((cc & 1) ? T(-1) : T(1));
+  const int mir = MIR == 2 ? Cols::mir(lrow) : 0, sig = Cols::sig(lrow);
+  T bop[LQ];
+  {
+    const auto q = w.pick(mir);
+    const T* c = reinterpret_cast<const T*>(coeffs + coef_offset(p.coff, b0 + min(sig, nb - 1), p.ncoef)) + (lrow & 1);
+    const T sg = ((((q.tm - q.tn) / 2) & 1) ? T(-1) : T(1)) * ((lrow & 1) ? T(-1) : T(1));
 #pragma unroll
     for (int s = 0; s < LQ; s++) {
-      bop[s][ct] = T(0);
+      bop[s] = T(0);
       if (s >= G) continue;
       const int j = 4 * s + lk, tl = q.tl0 + 2 * j;
       const bool ok = j < q.L && sig < nb;
@@ -417,45 +385,37 @@ __global__ __launch_bounds__(SMALL_INV_THREADS) void beta_inverse_small_kernel(c
         v = T(0.5) * (v + sg * c[ok ? 2 * coef_index_of(p.so3, tl, -q.tm, -q.tn) : 0]);
       // (2l+1) or 1, times the sign of a mirror column of a stored table
       const T sc = (p.scale_mode == 0 ? T(tl + 1) : T(1)) * (p.table_signs && q.tsign < 0 ? T(-1) : T(1));
-      bop[s][ct] = ok ? v * sc : T(0);
+      bop[s] = ok ? v * sc : T(0);
     }
   }
 
+  T* const mine = stages[0] + mir * 16 * ST::NRS + sig * ST::PB + 2 * (mir ? PT - 1 - wave : wave) + (lrow & 1);
   for (int kb = kb0; kb < kb1; kb++) {
-    accT acc[CT];
+    accT acc;
 #pragma unroll
-    for (int ct = 0; ct < CT; ct++)
-#pragma unroll
-      for (int r = 0; r < 4; r++) acc[ct][r] = T(0);
+    for (int r = 0; r < 4; r++) acc[r] = T(0);
 #pragma unroll
     for (int s = 0; s < LQ; s++)
-      if (s < G)
-#pragma unroll
-        for (int ct = 0; ct < CT; ct++) acc[ct] = mfma16x16x4(av[s], bop[s][ct], acc[ct]);
+      if (s < G) acc = mfma16x16x4(av[s], bop[s], acc);
     if (kb + 1 < kb1) fetch();  // next block's values, in flight during the stores
-    T* stage = stages[NST == 2 ? kb & 1 : 0];
-    if (NST == 1 && kb > kb0) __syncthreads();  // the previous block's rows are read
+    // two stage buffers in turn: one barrier per block
+    T* stage = stages[kb & 1];
 #pragma unroll
-    for (int ct = 0; ct < CT; ct++) {
-      const int cc = ct * 16 + lrow, mir = MIR == 2 ? Cols::mir(cc) : 0;
-      T* d = stage + mir * 16 * ST::NRS + Cols::sig(cc) * ST::PB + 2 * (mir ? PT - 1 - wave : wave) + (cc & 1);
-#pragma unroll
-      for (int r = 0; r < 4; r++) d[acc_row<T>(lane, r) * ST::NRS] = acc[ct][r];
-    }
+    for (int r = 0; r < 4; r++) mine[(kb & 1) * MIR * 16 * ST::NRS + acc_row<T>(lane, r) * ST::NRS] = acc[r];
     __syncthreads();
     // rows (node, signal) of PT pairs, 16 bytes per store
     constexpr int VC = 16 / (int)sizeof(cpx<T>), VPR = PT / VC;
     typedef T vec16 __attribute__((ext_vector_type(16 / sizeof(T))));
     const int mirs = MIR == 2 && p.ntiles - 1 - tile == tile ? 1 : MIR;  // a self-mirror tile once
     for (int v = tid; v < mirs * 16 * BT * VPR; v += SMALL_INV_THREADS) {
-      const int pv = v % VPR, bb = v / VPR % BT, kk = v / (VPR * BT) % 16, mir = v / (VPR * BT * 16);
+      const int pv = v % VPR, bb = v / VPR % BT, kk = v / (VPR * BT) % 16, h = v / (VPR * BT * 16);
       const int k = 16 * kb + kk;
       if (k >= N || bb >= nb) continue;
-      const T* src = stage + (mir * 16 + kk) * ST::NRS + bb * ST::PB + 2 * pv * VC;
+      const T* src = stage + (h * 16 + kk) * ST::NRS + bb * ST::PB + 2 * pv * VC;
       vec16 x;
 #pragma unroll
       for (int e = 0; e < 2 * VC; e++) x[e] = src[e];
-      const int t = mir ? p.ntiles - 1 - tile : tile;
+      const int t = h ? p.ntiles - 1 - tile : tile;
       *reinterpret_cast<vec16*>(S + (((size_t)t * N + k) * p.batch + b0 + bb) * PT + pv * VC) = x;
     }
   }
@@ -466,72 +426,89 @@ __global__ __launch_bounds__(SMALL_INV_THREADS) void beta_inverse_small_kernel(c
 template <class T>
 static bool small_mirrored(const BetaParams<T>& p) { return p.sym && !p.real; }
 
-// Up to 8 signals; above, the tile kernels' staged tables serve enough columns
-// (B = 64 FP32, 12 signals: forward 46 us against 72, inverse 34 against 58).
-// The inverse up to 8 degrees (B <= 16) stays with the tile kernel, as fast and
-// smaller.  Forward / inverse, us, tile kernel -> these: B = 64 FP32, 1 signal
-// 42 -> 14 / 27 -> 13, 8 signals 45 -> 31 / 31 -> 25; FP64, 1 signal 57 -> 15 /
-// 53 -> 19; B = 36 FP32, 1 signal 16 -> 7 / 12 -> 7; B = 128 FP64, 1 signal
-// 795 -> 241 / 745 -> 263 (the table alone takes 133 at the copy rate).
-constexpr int SMALL_BATCH = 8;
+// pair tiles (with their mirrors) of a launch
 template <class T>
-bool beta_small_forward(const BetaParams<T>& p) { return p.batch <= SMALL_BATCH; }
+static long long small_units(const BetaParams<T>& p) {
+  return small_mirrored(p) ? (p.ntiles + 1) / 2 : p.ntiles - p.tile0;
+}
+// enough tiles that workgroups of one tile each reach three of four CUs
 template <class T>
-bool beta_small_inverse(const BetaParams<T>& p) { return p.batch <= SMALL_BATCH && p.B > 16; }
+static bool small_fills(const BetaParams<T>& p) { return 4 * small_units(p) >= 3LL * device_cus(); }
 
-// Forward with the spectra through LDS: where the lines of S that the
-// LDS-free kernel reads piecemeal outweigh the barriers, i.e. by signals times
-// tiles, and only with enough tiles to give most CUs a workgroup.  LDS-free ->
-// through LDS, us: FP32 B = 128, 1 signal 144 -> 123, 2 signals 202 -> 132; B = 96,
-// 1 signal 41 -> 46, 4 signals 76 -> 53; B = 64, 2 signals 15.1 -> 15.4, 8 signals
-// 42 -> 31; B = 48 (142 tiles), 4 signals 10 -> 12.  FP64, whose products take
-// twice as long and whose chunks hold half the nodes, B = 64, 2 signals
-// 20 -> 23, 4 signals 28 -> 26; B = 128, 1 signal 241 -> 251, 2 signals 302 -> 266.
+// Forward: these kernels instead of the tile kernel where its grid of tiles and
+// 16- or 32-signal groups leaves CUs idle or columns empty, i.e. by signals
+// times tiles; with a tile per CU or more, by signals.  Tile kernel -> these, us:
+// FP32 B = 24, 48 signals 11.5 -> 11.1, 64 signals 14.4 -> 14.9; B = 36, 17 signals
+// 21 -> 13, 48 signals 26 -> 34; B = 64, 1 signal 42 -> 14, 8 signals 45 -> 30,
+// 12 signals 46 -> 41, 16 signals 47 -> 53; B = 72, 16 signals 89 -> 62; B = 128,
+// 1 signal 371 -> 123.  FP64 B = 36, 24 signals 38 -> 23; B = 64, 1 signal
+// 57 -> 15, 12 signals 60 -> 57, 16 signals 69 -> 90; B = 128, 1 signal 795 -> 241 (the
+// table alone takes 133 at the copy rate).
 template <class T>
-static bool small_through_lds(const BetaParams<T>& p) {
-  const long long units = small_mirrored(p) ? (p.ntiles + 1) / 2 : p.ntiles - p.tile0;
-  return 4 * units >= 3LL * device_cus() && (2LL * p.batch - 1) * units >= (sizeof(T) == 4 ? 750 : 1750);
+bool beta_small_forward(const BetaParams<T>& p) {
+  if (small_fills(p)) return p.batch <= (p.B > 64 ? 16 : 12);
+  return p.batch * small_units(p) <= (sizeof(T) == 4 ? 1900 : 2700);
 }
 
-template <class T, int CT, int MIR>
+// Inverse: likewise (its tile kernel also gathers the coefficients through
+// eight barriers); up to 8 degrees the tile kernel is as fast and smaller.  Tile
+// kernel -> this, us: FP32 B = 32, 48 signals 15.8 -> 15.0, 64 signals 17.7 -> 18.5;
+// B = 36, 17 signals 17.5 -> 12; B = 64, 1 signal 27 -> 13, 12 signals 33.9 -> 33.2,
+// 24 signals 54.7 -> 55.9; B = 96, 12 signals 171 -> 143.  FP64 B = 48, 12 signals
+// 34 -> 22; B = 64, 1 signal 53 -> 19, 9 signals 56 -> 46, 12 signals 62 -> 68; B = 96,
+// 12 signals 354 -> 304.
+template <class T>
+bool beta_small_inverse(const BetaParams<T>& p) {
+  const int lq = beta_lq(p.B);
+  if (lq == 2) return false;
+  if (lq == 16) return p.batch <= 16;
+  return p.batch * small_units(p) <= (sizeof(T) == 4 ? 4000 : 2900);
+}
+
+// Forward with the spectra through LDS: where the lines of S that the
+// LDS-free kernel reads piecemeal outweigh the barriers, and only with enough
+// tiles to give most CUs a workgroup.  LDS-free -> through LDS, us: FP32 B = 128,
+// 1 signal 144 -> 123, 2 signals 202 -> 132; B = 96, 1 signal 41 -> 46, 3 signals
+// 62 -> 49; B = 64, 2 signals 14.9 -> 15.4, 8 signals 37 -> 30; B = 48 (142 tiles),
+// 8 signals 15 -> 20.  FP64, whose products take twice as long and whose chunks
+// hold half the nodes, B = 64, 2 signals 19 -> 22, 5 signals 43 -> 37; B = 96, 2 signals
+// 102 -> 112, 3 signals 128 -> 118.
+template <class T>
+static bool small_through_lds(const BetaParams<T>& p) {
+  return small_fills(p) && p.batch * small_units(p) >= (sizeof(T) == 4 ? 1000 : 1250);
+}
+
+template <class T, int MIR>
 static hipError_t launch_forward_mid(const BetaParams<T>& p, const cpx<T>* S, cpx<T>* coeffs, hipStream_t s) {
-  constexpr int BT = SmallCols<MIR, CT>::BT;
+  constexpr int BT = SmallCols<MIR>::BT;
   const int pos_end = MIR == 2 ? p.ntiles * PT / 2 : p.ntiles * PT;
   const int ntl = (pos_end - p.tile0 * PT + PT - 1) / PT, nbt = (p.batch + BT - 1) / BT;
   const dim3 grid(contraction_grid(ntl, nbt)), block(MID_THREADS);
   switch (beta_rtmax(p.B)) {
-    case 1: hipLaunchKernelGGL((beta_forward_mid_kernel<T, 1, CT, MIR>), grid, block, 0, s, S, coeffs, p, pos_end); break;
-    case 2: hipLaunchKernelGGL((beta_forward_mid_kernel<T, 2, CT, MIR>), grid, block, 0, s, S, coeffs, p, pos_end); break;
-    default: hipLaunchKernelGGL((beta_forward_mid_kernel<T, 4, CT, MIR>), grid, block, 0, s, S, coeffs, p, pos_end); break;
+    case 1: hipLaunchKernelGGL((beta_forward_mid_kernel<T, 1, MIR>), grid, block, 0, s, S, coeffs, p, pos_end); break;
+    case 2: hipLaunchKernelGGL((beta_forward_mid_kernel<T, 2, MIR>), grid, block, 0, s, S, coeffs, p, pos_end); break;
+    default: hipLaunchKernelGGL((beta_forward_mid_kernel<T, 4, MIR>), grid, block, 0, s, S, coeffs, p, pos_end); break;
   }
   return hipGetLastError();
 }
 
-template <class T, int CT, int MIR>
+template <class T, int MIR>
 static hipError_t launch_forward_small(const BetaParams<T>& p, const cpx<T>* S, cpx<T>* coeffs, hipStream_t s) {
-  constexpr int BT = SmallCols<MIR, CT>::BT;
+  constexpr int BT = SmallCols<MIR>::BT;
   const int pos_end = MIR == 2 ? p.ntiles * PT / 2 : p.ntiles * PT;
   const int ntl = (pos_end - p.tile0 * PT + PT - 1) / PT, nbt = (p.batch + BT - 1) / BT;
   const dim3 grid(contraction_grid(ntl, PT / SMALL_FWD_WAVES * nbt)), block(64 * SMALL_FWD_WAVES);
   switch (beta_rtmax(p.B)) {
-    case 1: hipLaunchKernelGGL((beta_forward_small_kernel<T, 1, CT, MIR>), grid, block, 0, s, S, coeffs, p, pos_end); break;
-    case 2: hipLaunchKernelGGL((beta_forward_small_kernel<T, 2, CT, MIR>), grid, block, 0, s, S, coeffs, p, pos_end); break;
-    default: hipLaunchKernelGGL((beta_forward_small_kernel<T, 4, CT, MIR>), grid, block, 0, s, S, coeffs, p, pos_end); break;
+    case 1: hipLaunchKernelGGL((beta_forward_small_kernel<T, 1, MIR>), grid, block, 0, s, S, coeffs, p, pos_end); break;
+    case 2: hipLaunchKernelGGL((beta_forward_small_kernel<T, 2, MIR>), grid, block, 0, s, S, coeffs, p, pos_end); break;
+    default: hipLaunchKernelGGL((beta_forward_small_kernel<T, 4, MIR>), grid, block, 0, s, S, coeffs, p, pos_end); break;
   }
   return hipGetLastError();
 }
 
-// products side by side that the inverse has registers for (16 waves per
-// workgroup: at most 128 per lane)
-template <class T, int LQ, int CT>
-constexpr int small_inverse_ct() {
-  constexpr int most = sizeof(T) == 4 ? (LQ == 16 ? 2 : 4) : (LQ == 16 ? 1 : (LQ == 8 ? 2 : 4));
-  return CT < most ? CT : most;
-}
-
-template <class T, int LQ, int CT, int MIR>
+template <class T, int LQ, int MIR>
 static hipError_t launch_inverse_small_lq(const BetaParams<T>& p, const cpx<T>* coeffs, cpx<T>* S, hipStream_t s) {
-  constexpr int BT = SmallCols<MIR, CT>::BT;
+  constexpr int BT = SmallCols<MIR>::BT;
   const int ntl = MIR == 2 ? (p.ntiles + 1) / 2 : p.ntiles - p.tile0, nbt = (p.batch + BT - 1) / BT;
   const int NB = (p.N + 15) / 16;
   // node blocks per workgroup: the fewest block times, counting the coefficient
@@ -547,35 +524,29 @@ static hipError_t launch_inverse_small_lq(const BetaParams<T>& p, const cpx<T>* 
     }
   }
   const dim3 grid(contraction_grid(ntl, (NB + blocks - 1) / blocks * nbt)), block(SMALL_INV_THREADS);
-  hipLaunchKernelGGL((beta_inverse_small_kernel<T, LQ, CT, MIR>), grid, block, 0, s, coeffs, S, p, ntl, blocks);
+  hipLaunchKernelGGL((beta_inverse_small_kernel<T, LQ, MIR>), grid, block, 0, s, coeffs, S, p, ntl, blocks);
   return hipGetLastError();
 }
 
-template <class T, int CT, int MIR>
+template <class T, int MIR>
 static hipError_t launch_inverse_small(const BetaParams<T>& p, const cpx<T>* coeffs, cpx<T>* S, hipStream_t s) {
   switch (beta_lq(p.B)) {
-    case 2: return launch_inverse_small_lq<T, 2, small_inverse_ct<T, 2, CT>(), MIR>(p, coeffs, S, s);
-    case 4: return launch_inverse_small_lq<T, 4, small_inverse_ct<T, 4, CT>(), MIR>(p, coeffs, S, s);
-    case 8: return launch_inverse_small_lq<T, 8, small_inverse_ct<T, 8, CT>(), MIR>(p, coeffs, S, s);
-    default: return launch_inverse_small_lq<T, 16, small_inverse_ct<T, 16, CT>(), MIR>(p, coeffs, S, s);
+    case 4: return launch_inverse_small_lq<T, 4, MIR>(p, coeffs, S, s);
+    case 8: return launch_inverse_small_lq<T, 8, MIR>(p, coeffs, S, s);
+    case 16: return launch_inverse_small_lq<T, 16, MIR>(p, coeffs, S, s);
   }
+  return hipErrorInvalidValue;
 }
 
-// products per wave side by side: the narrowest that hold the batch
 template <class T>
 hipError_t launch_beta_forward_small(const BetaParams<T>& p, const cpx<T>* S, cpx<T>* coeffs, hipStream_t s) {
-  const bool mid = small_through_lds(p);
-  if (!small_mirrored(p))
-    return mid ? launch_forward_mid<T, 1, 1>(p, S, coeffs, s) : launch_forward_small<T, 1, 1>(p, S, coeffs, s);
-  if (p.batch <= 4)
-    return mid ? launch_forward_mid<T, 1, 2>(p, S, coeffs, s) : launch_forward_small<T, 1, 2>(p, S, coeffs, s);
-  return mid ? launch_forward_mid<T, 2, 2>(p, S, coeffs, s) : launch_forward_small<T, 2, 2>(p, S, coeffs, s);
+  if (small_mirrored(p))
+    return small_through_lds(p) ? launch_forward_mid<T, 2>(p, S, coeffs, s) : launch_forward_small<T, 2>(p, S, coeffs, s);
+  return small_through_lds(p) ? launch_forward_mid<T, 1>(p, S, coeffs, s) : launch_forward_small<T, 1>(p, S, coeffs, s);
 }
 template <class T>
 hipError_t launch_beta_inverse_small(const BetaParams<T>& p, const cpx<T>* coeffs, cpx<T>* S, hipStream_t s) {
-  if (!small_mirrored(p)) return launch_inverse_small<T, 1, 1>(p, coeffs, S, s);
-  if (p.batch <= 4) return launch_inverse_small<T, 1, 2>(p, coeffs, S, s);
-  return launch_inverse_small<T, 2, 2>(p, coeffs, S, s);
+  return small_mirrored(p) ? launch_inverse_small<T, 2>(p, coeffs, S, s) : launch_inverse_small<T, 1>(p, coeffs, S, s);
 }
 
 template bool beta_small_forward<float>(const BetaParams<float>&);
