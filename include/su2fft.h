@@ -137,7 +137,7 @@ su2_status_t su2_plan_create_ex(int32_t B, int32_t batch, su2_dtype_t dtype, uin
  * the per-signal sizes (su2_num_samples / su2_num_coeffs of its B).  A call
  * runs as work-list launches covering every signal (ring FFTs, then
  * contractions, or the reverse); they are captured into a HIP graph the
- * first time a (direction, input, output, stream) combination is used, and
+ * second time a (direction, input, output, stream) combination is used, and
  * the graph is replayed on later calls with the same buffers and stream (the
  * plan keeps up to 16 such graphs).  Results are bit-identical to single-B
  * plans of each signal (B = 128 groups run the single-B plan's N = 256 ring

@@ -152,6 +152,14 @@ def _stream_handle(device) -> ctypes.c_void_p:
     return ctypes.c_void_p(torch.cuda.current_stream(device).cuda_stream)
 
 
+# current stream of a device index as an integer, without building a Stream
+# object (1.9 -> 0.1 us of every call's host time)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+if _raw_stream is None:
+    def _raw_stream(index: int) -> int:
+        return torch.cuda.current_stream(index).cuda_stream
+
+
 def _device_buffer(t, what: str):
     if not (isinstance(t, torch.Tensor) and t.is_cuda and t.is_contiguous()):
         raise ValueError(f"{what}: a contiguous device tensor is required")
@@ -206,9 +214,10 @@ class _PlanBase:
             raise ValueError(f"{what} is on {t.device}, plan is on {self.device}")
 
     def _call(self, fn: str, src: torch.Tensor, dst: torch.Tensor):
-        status = getattr(_load(), fn)(self._handle, ctypes.c_void_p(src.data_ptr()),
-                                      ctypes.c_void_p(dst.data_ptr()), _stream_handle(self.device))
-        _check(status, fn)
+        # plain integers: ctypes converts them as the declared void pointers
+        status = getattr(_lib, fn)(self._handle, src.data_ptr(), dst.data_ptr(), _raw_stream(self.device.index))
+        if status != 0:
+            _check(status, fn)
 
     @property
     def sample_dtype(self):
@@ -219,7 +228,8 @@ class _PlanBase:
         self._check_tensor(samples, self.total_samples, "samples", self.sample_dtype)
         if out is None:
             out = torch.empty(self.coeff_shape, dtype=self.torch_dtype, device=self.device)
-        self._check_tensor(out, self.total_coeffs, "out")
+        else:
+            self._check_tensor(out, self.total_coeffs, "out")
         self._call("su2_forward", samples, out)
         return out
 
@@ -236,7 +246,8 @@ class _PlanBase:
         self._check_tensor(coeffs, self.total_coeffs, "coeffs")
         if out is None:
             out = torch.empty(self.sample_shape, dtype=self.sample_dtype, device=self.device)
-        self._check_tensor(out, self.total_samples, "out", self.sample_dtype)
+        else:
+            self._check_tensor(out, self.total_samples, "out", self.sample_dtype)
         self._call("su2_inverse", coeffs, out)
         return out
 
@@ -244,7 +255,8 @@ class _PlanBase:
         self._check_tensor(coeffs, self.total_coeffs, "coeffs")
         if out is None:
             out = torch.empty(self.sample_shape, dtype=self.sample_dtype, device=self.device)
-        self._check_tensor(out, self.total_samples, "out", self.sample_dtype)
+        else:
+            self._check_tensor(out, self.total_samples, "out", self.sample_dtype)
         self._call("su2_adjoint", coeffs, out)
         return out
 
