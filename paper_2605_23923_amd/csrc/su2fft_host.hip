@@ -693,6 +693,36 @@ su2_status_t run_pair(su2_plan_s* pl, su2_stage_t first, su2_stage_t second, con
   return run_stage(pl, second, nullptr, out, s, S);
 }
 
+// One kernel per call for grids up to N = 16 (su2fft_fused.h): stored tables in
+// the type of the transform, every pair contracted.  Two kernels -> one, us,
+// forward / inverse: FP64 B = 8, 1 signal 8.6 -> 7.6 / 10.1 -> 8.2, 256 signals
+// 15.0 -> 10.4 / 15.8 -> 11.3; B = 6, 1 signal 7.8 -> 5.5 / 7.8 -> 6.1; FP32 B = 4,
+// 1 signal 6.5 -> 3.5 / 6.7 -> 4.2.  At B = 9 one workgroup's rings and products
+// take longer than a second launch (FP64, 1 signal 7.6 -> 14.4 / 10.8 -> 13.2).
+bool fused_call(const su2_plan_s* pl) {
+  return pl->B <= 8 && !pl->otf && pl->dtype != SU2_C64_BF16X3 && !(pl->real && !pl->real_io);
+}
+template <class T>
+su2_status_t run_fused(su2_plan_s* pl, bool forward, int adjoint, const void* in, void* out, hipStream_t s) {
+  const BetaParams<T> q = beta_params<T>(pl, table_of<T>(pl), adjoint);
+  const hipError_t e =
+      pl->fast ? launch_fast_fused<T>(forward, fast_params<T>(pl, adjoint), q, (const cpx<T>*)in, (cpx<T>*)out,
+                                      (cpx<T>*)pl->d_S, s)
+               : launch_radix_fused<T>(forward, radix_params<T>(pl, adjoint), q, (const cpx<T>*)in, (cpx<T>*)out,
+                                       (cpx<T>*)pl->d_S, s);
+  return e == hipSuccess ? SU2_OK : hip_fail(e);
+}
+
+// a whole call of a single-B plan
+su2_status_t run_call(su2_plan_s* pl, bool forward, int adjoint, const void* in, void* out, hipStream_t s) {
+  if (fused_call(pl))
+    return pl->dtype == SU2_C128 ? run_fused<double>(pl, forward, adjoint, in, out, s)
+                                 : run_fused<float>(pl, forward, adjoint, in, out, s);
+  if (forward) return run_pair(pl, SU2_STAGE_RING_FORWARD, SU2_STAGE_BETA_FORWARD, in, out, s);
+  return adjoint ? run_pair(pl, SU2_STAGE_BETA_ADJOINT, SU2_STAGE_RING_ADJOINT, in, out, s)
+                 : run_pair(pl, SU2_STAGE_BETA_INVERSE, SU2_STAGE_RING_INVERSE, in, out, s);
+}
+
 su2_status_t check_device() {
   int count = 0;
   hipError_t e = hipGetDeviceCount(&count);
@@ -847,19 +877,19 @@ su2_status_t su2_plan_info(su2_plan_t plan, int32_t* B, int32_t* batch, int32_t*
 su2_status_t su2_forward(su2_plan_t plan, const void* d_samples, void* d_coeffs, hipStream_t stream) {
   if (!plan || !d_samples || !d_coeffs) return SU2_ERR_INVALID_VALUE;
   if (plan->mixed) return run_mixed(plan, 0, d_samples, d_coeffs, stream);
-  return run_pair(plan, SU2_STAGE_RING_FORWARD, SU2_STAGE_BETA_FORWARD, d_samples, d_coeffs, stream);
+  return run_call(plan, true, 0, d_samples, d_coeffs, stream);
 }
 
 su2_status_t su2_inverse(su2_plan_t plan, const void* d_coeffs, void* d_samples, hipStream_t stream) {
   if (!plan || !d_samples || !d_coeffs) return SU2_ERR_INVALID_VALUE;
   if (plan->mixed) return run_mixed(plan, 1, d_coeffs, d_samples, stream);
-  return run_pair(plan, SU2_STAGE_BETA_INVERSE, SU2_STAGE_RING_INVERSE, d_coeffs, d_samples, stream);
+  return run_call(plan, false, 0, d_coeffs, d_samples, stream);
 }
 
 su2_status_t su2_adjoint(su2_plan_t plan, const void* d_coeffs, void* d_samples, hipStream_t stream) {
   if (!plan || !d_samples || !d_coeffs) return SU2_ERR_INVALID_VALUE;
   if (plan->mixed) return run_mixed(plan, 2, d_coeffs, d_samples, stream);
-  return run_pair(plan, SU2_STAGE_BETA_ADJOINT, SU2_STAGE_RING_ADJOINT, d_coeffs, d_samples, stream);
+  return run_call(plan, false, 1, d_coeffs, d_samples, stream);
 }
 
 su2_status_t su2_forward_noalloc(su2_plan_t plan, const void* d_samples, void* d_coeffs, hipStream_t stream) {

@@ -300,6 +300,10 @@ template <class T>
 hipError_t launch_beta_forward(const BetaParams<T>& p, const cpx<T>* S, cpx<T>* coeffs, hipStream_t s);
 template <class T>
 hipError_t launch_beta_inverse(const BetaParams<T>& p, const cpx<T>* coeffs, cpx<T>* S, hipStream_t s);
+// whole signals in one kernel, spectra in LDS (N <= 12; launch_fast_fused: N = 16); S: the plan's workspace
+template <class T>
+hipError_t launch_radix_fused(bool forward, const RadixRingParams<T>& p, const BetaParams<T>& q, const cpx<T>* in,
+                              cpx<T>* out, cpx<T>* S, hipStream_t s);
 // small batches (su2fft_beta_small.hip): whether the streaming kernels take a
 // call, and their launches
 template <class T>
@@ -365,6 +369,10 @@ template <class T>
 hipError_t launch_ring_forward_fast_real(const FastRingParams<T>& p, const T* samples, cpx<T>* S, hipStream_t s);
 template <class T>
 hipError_t launch_ring_inverse_fast_real(const FastRingParams<T>& p, const cpx<T>* S, T* samples, hipStream_t s);
+
+template <class T>
+hipError_t launch_fast_fused(bool forward, const FastRingParams<T>& p, const BetaParams<T>& q, const cpx<T>* in,
+                             cpx<T>* out, cpx<T>* S, hipStream_t s);
 
 bool large_ring_supported(int N);
 int large_ring_block();           // gamma frequencies per block (pair ranges are given per block)

@@ -21,7 +21,7 @@
 // for smaller N the workgroup is split into sub-groups of NTR threads, each
 // with its own slice of LDS, working on consecutive rings of one signal (the
 // sub-groups run the same code, so the workgroup barriers line up).
-#include "su2fft_internal.h"
+#include "su2fft_fused.h"
 
 namespace su2 {
 
@@ -770,6 +770,64 @@ __global__ __launch_bounds__(FAST_NT, fast_waves_per_simd<T>()) void ring_invers
   ring_inverse_fast_transform<T, N1, N2, NT, FAST_ROUNDS, REAL>(sv, ent, scale, p, buf, tw, a, t2);
   ring_inverse_fast_store<T, N1, N2, NT, REAL>(a, xo + (size_t)(k0 + 1) * N * N, t2);
 }
+
+// Whole signals at N = 16: the workgroup's 16 sub-groups transform the 16 rings
+// of one signal, with the spectra in LDS between rings and contraction (see
+// su2fft_fused.h; they go to the plan's workspace as well).
+template <class T, bool FWD>
+__global__ __launch_bounds__(FAST_NT, fast_waves_per_simd<T>()) void ring_fast_fused_kernel(
+    const cpx<T>* __restrict__ in, cpx<T>* __restrict__ out, cpx<T>* __restrict__ Sg, FastRingParams<T> p,
+    BetaParams<T> q) {
+  constexpr int N = 16;
+  typedef FastRing<T, N> R;
+  typedef FastCfg<N> C;
+  static_assert(R::RPW == N, "one signal per workgroup");
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  const int t = threadIdx.x, b = blockIdx.x, k = t / C::NTR, tr = t - k * C::NTR, batch = p.batch;
+  const int ns = q.ntiles * PT * N;
+  cpx<T>* Sl = reinterpret_cast<cpx<T>*>(smem_raw + R::SMEM);
+  const size_t x0 = ring_offset(p.soff, b, N) + (size_t)k * N * N, c0 = coef_offset(q.coff, b, q.ncoef);
+  p.batch = 1;  // the spectra in LDS are this signal's alone
+  if constexpr (FWD) {
+    ring_forward_fast_body<T, C::N1, C::N2, C::NTR, FAST_ROUNDS, false>(in + x0, Sl, p, 0, k,
+                                                                        smem_raw + k * R::RING_SMEM, tr);
+    __syncthreads();
+    fused_contract_forward<T, N, FAST_NT>(Sl, out + c0, q, t);
+    for (int e = t; e < ns; e += FAST_NT) Sg[((size_t)(e / PT) * batch + b) * PT + e % PT] = Sl[e];
+  } else {
+    cpx<T>* Cl = Sl + ns;
+    for (int e = t; e < (int)q.ncoef; e += FAST_NT) Cl[e] = in[c0 + e];
+    __syncthreads();
+    fused_contract_inverse<T, N, FAST_NT>(Cl, Sl, q, t);
+    __syncthreads();
+    for (int e = t; e < ns; e += FAST_NT) Sg[((size_t)(e / PT) * batch + b) * PT + e % PT] = Sl[e];
+    ring_inverse_fast_body<T, C::N1, C::N2, C::NTR, FAST_ROUNDS, false>(Sl, out + x0, p, 0, k,
+                                                                        smem_raw + k * R::RING_SMEM, tr);
+  }
+}
+
+template <class T>
+hipError_t launch_fast_fused(bool forward, const FastRingParams<T>& p, const BetaParams<T>& q, const cpx<T>* in,
+                             cpx<T>* out, cpx<T>* Sg, hipStream_t s) {
+  typedef FastRing<T, 16> R;
+  if (p.N != 16) return hipErrorInvalidValue;
+  for (int r = 0; r < FAST_ROUNDS; r++)
+    if (p.rend[r] - p.rbeg[r] > R::G::SLICE_CAP) return hipErrorInvalidValue;
+  const size_t smem = R::SMEM + ((size_t)q.ntiles * PT * 16 + (forward ? 0 : q.ncoef)) * sizeof(cpx<T>);
+  const void* kern = forward ? (const void*)ring_fast_fused_kernel<T, true> : (const void*)ring_fast_fused_kernel<T, false>;
+  if (smem > 64 * 1024) {
+    const hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+    if (e != hipSuccess) return e;
+  }
+  FastRingParams<T> pp = p;
+  BetaParams<T> qq = q;
+  void* args[] = {(void*)&in, (void*)&out, (void*)&Sg, (void*)&pp, (void*)&qq};
+  return hipLaunchKernel(kern, dim3(p.batch), dim3(FAST_NT), args, smem, s);
+}
+template hipError_t launch_fast_fused<float>(bool, const FastRingParams<float>&, const BetaParams<float>&,
+                                             const cpx<float>*, cpx<float>*, cpx<float>*, hipStream_t);
+template hipError_t launch_fast_fused<double>(bool, const FastRingParams<double>&, const BetaParams<double>&,
+                                              const cpx<double>*, cpx<double>*, cpx<double>*, hipStream_t);
 
 template <class T>
 bool fast_ring_supported(int N) {

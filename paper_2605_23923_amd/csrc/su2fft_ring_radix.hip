@@ -44,7 +44,7 @@
 // signals 291 / 293 -> 99 / 94 us; N = 72 FP32, 44 signals 140 / 142 -> 49 / 54 us;
 // N = 96 FP32, 18 signals 93 / 83 -> 47 / 59 us; N = 192 FP32, 2 signals
 // 278 / 280 -> 62 / 74 us; N = 216 FP64, 2 signals 799 / 968 -> 264 / 228 us.
-#include "su2fft_internal.h"
+#include "su2fft_fused.h"
 
 namespace su2 {
 
@@ -690,6 +690,116 @@ static hipError_t launch_radix_any(const RadixRingParams<T>& p, const cpx<T>* in
   }
   return hipErrorInvalidValue;
 }
+
+// ---- whole signals: rings and contraction in one kernel (N <= 12) ----
+//
+// One workgroup per signal: its rings, one sub-group each, into spectra kept in LDS,
+// and the contraction from there (su2fft_fused.h); the inverse the other way
+// round.  The spectra go to the plan's workspace as well, where the stage by
+// stage launches leave them.
+template <class T, int N, bool FWD>
+struct FusedShape {
+  typedef RadixCfg<T, N, FWD> C;
+  typedef typename std::conditional<FWD, RadixForward<T, N, C>, RadixInverse<T, N, C>>::type X;
+  static_assert(C::R == 1, "whole rings");
+  static constexpr int NT = N == 12 ? 768 : 512, NTR = C::NTR;  // 12 wavefronts for the 12 rings at N = 12
+  static_assert(N * NTR <= NT, "a sub-group per ring");
+};
+
+template <class T, int N, bool FWD>
+static size_t fused_smem(const BetaParams<T>& q) {
+  typedef FusedShape<T, N, FWD> F;
+  return sizeof(int4) * N +
+         (2 * N + (size_t)q.ntiles * PT * N + (size_t)N * F::X::LDS + (FWD ? 0 : q.ncoef)) * sizeof(cpx<T>);
+}
+
+template <class T, int N, bool FWD>
+__global__ __launch_bounds__((FusedShape<T, N, FWD>::NT)) void radix_fused_kernel(const cpx<T>* __restrict__ in,
+                                                                                cpx<T>* __restrict__ out,
+                                                                                cpx<T>* __restrict__ Sg,
+                                                                                RadixRingParams<T> p, BetaParams<T> q) {
+  typedef FusedShape<T, N, FWD> F;
+  typedef typename F::X X;
+  constexpr int NT = F::NT;
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  int4* cols = reinterpret_cast<int4*>(smem_raw);
+  cpx<T>* tw = reinterpret_cast<cpx<T>*>(cols + N);
+  const int ns = q.ntiles * PT * N;
+  cpx<T>* Sl = tw + 2 * N;
+  cpx<T>* bufs = Sl + ns;
+  const int t = threadIdx.x, b = blockIdx.x, k = t / F::NTR, tr = t - k * F::NTR;
+  const size_t x0 = ring_offset(p.soff, b, N), c0 = coef_offset(q.coff, b, q.ncoef);
+  for (int u = t; u < N; u += NT) cols[u] = p.cols[u];
+  for (int u = t; u < 2 * N; u += NT) tw[u] = p.tw[u];
+  const bool ok = k < N;
+  cpx<T>* buf = bufs + (ok ? k : 0) * X::LDS;
+  const size_t xk = x0 + (size_t)k * N * N;
+  if constexpr (FWD) {
+    __syncthreads();
+    const cpx<T>* x = p.real_io ? reinterpret_cast<const cpx<T>*>(reinterpret_cast<const T*>(in) + xk) : in + xk;
+    if (ok) X::forward1(x, buf, tw, p.tw, 0, p.real_io, tr);
+    __syncthreads();
+    if (ok) X::forward2(buf, tr);
+    __syncthreads();
+    if (ok) X::forward3(buf, tw, 0, p.so3, tr);
+    __syncthreads();
+    if (ok) X::forward4(buf, tr);
+    __syncthreads();
+    if (ok) X::forward5(buf, Sl + k * PT, (size_t)N * PT, cols, p.W[k], 0, tr);
+    __syncthreads();
+    fused_contract_forward<T, N, NT>(Sl, out + c0, q, t);
+    for (int e = t; e < ns; e += NT)
+      Sg[((size_t)(e / PT) * p.batch + b) * PT + e % PT] = Sl[e];
+  } else {
+    cpx<T>* Cl = bufs + N * X::LDS;
+    for (int e = t; e < (int)q.ncoef; e += NT) Cl[e] = in[c0 + e];
+    __syncthreads();
+    fused_contract_inverse<T, N, NT>(Cl, Sl, q, t);
+    __syncthreads();
+    for (int e = t; e < ns; e += NT)
+      Sg[((size_t)(e / PT) * p.batch + b) * PT + e % PT] = Sl[e];
+    cpx<T>* x = p.real_io ? reinterpret_cast<cpx<T>*>(reinterpret_cast<T*>(out) + xk) : out + xk;
+    if (ok) X::inverse1(Sl + k * PT, (size_t)N * PT, buf, tw, p.tw, cols, p.adjoint ? p.W[k] : T(1), 0, tr);
+    __syncthreads();
+    if (ok) X::inverse2(buf, tw, 0, p.so3, tr);
+    __syncthreads();
+    if (ok) X::inverse3(buf, tw, tr);
+    __syncthreads();
+    if (ok) X::inverse4(buf, x, 0, p.real_io, tr);
+    __syncthreads();
+  }
+}
+
+template <class T, int N, bool FWD>
+static hipError_t launch_fused(const RadixRingParams<T>& p, const BetaParams<T>& q, const cpx<T>* in, cpx<T>* out,
+                               cpx<T>* Sg, hipStream_t s) {
+  const size_t smem = fused_smem<T, N, FWD>(q);
+  if (smem > 160 * 1024) return hipErrorInvalidValue;
+  if (smem > 64 * 1024) {
+    const hipError_t e = hipFuncSetAttribute((const void*)radix_fused_kernel<T, N, FWD>,
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL((radix_fused_kernel<T, N, FWD>), dim3(p.batch), dim3(FusedShape<T, N, FWD>::NT), smem, s, in, out,
+                     Sg, p, q);
+  return hipGetLastError();
+}
+
+template <class T>
+hipError_t launch_radix_fused(bool forward, const RadixRingParams<T>& p, const BetaParams<T>& q, const cpx<T>* in,
+                              cpx<T>* out, cpx<T>* Sg, hipStream_t s) {
+  switch (p.N) {
+#define SU2_FUSED_CASE(NN) \
+  case NN: return forward ? launch_fused<T, NN, true>(p, q, in, out, Sg, s) : launch_fused<T, NN, false>(p, q, in, out, Sg, s);
+    SU2_FUSED_CASE(2) SU2_FUSED_CASE(4) SU2_FUSED_CASE(6) SU2_FUSED_CASE(8) SU2_FUSED_CASE(12)
+#undef SU2_FUSED_CASE
+  }
+  return hipErrorInvalidValue;
+}
+template hipError_t launch_radix_fused<float>(bool, const RadixRingParams<float>&, const BetaParams<float>&,
+                                              const cpx<float>*, cpx<float>*, cpx<float>*, hipStream_t);
+template hipError_t launch_radix_fused<double>(bool, const RadixRingParams<double>&, const BetaParams<double>&,
+                                               const cpx<double>*, cpx<double>*, cpx<double>*, hipStream_t);
 
 template <class T>
 hipError_t launch_ring_forward_radix(const RadixRingParams<T>& p, const cpx<T>* samples, cpx<T>* S, hipStream_t s) {
