@@ -18,7 +18,7 @@ RESOURCES = os.path.join(HERE, "kernel_resources.json")
 # su2fft_kernels.hip includes su2fft_ring_fast.hip, su2fft_beta.hip,
 # su2fft_beta_bf16.hip and the other kernels that mixed plans' work lists run
 # too; the sources below are compiled side by side and linked
-SOURCES = ["su2fft_kernels.hip", "su2fft_ring_radix.hip", "su2fft_beta_small.hip", "su2fft_host.hip", "su2fft_table.hip", "su2fft_calib.hip"]
+SOURCES = ["su2fft_kernels.hip", "su2fft_ring_radix.hip", "su2fft_beta_small.hip", "su2fft_beta_bf16_small.hip", "su2fft_host.hip", "su2fft_table.hip", "su2fft_calib.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 FLAGS = [

@@ -5,53 +5,9 @@
 // about 2^-16 relative, is dropped).  The contraction itself is the one of
 // the FP32 path (the inner products <s, P^l_{nm}> of Section 4 for every
 // pair); only the arithmetic of the matrix products changes.
-//
-// Instruction: V_MFMA_F32_16X16X32_BF16, A 16x32, B 32x16, lane l holding
-// A[l % 16][8 (l / 16) + i] and B[8 (l / 16) + i][l % 16], i = 0..7, and
-// the accumulator D[4 (l / 16) + r][l % 16] (all measured).
-//
-// Tables (hi in the low 16 bits, lo in the high 16 bits of a 32-bit word):
-//   forward: [tile][k / 8][column j = coff + i][k % 8]  (a lane's 8 nodes are
-//            one aligned 32-byte load), rows k >= N zero;
-//   inverse: the tile-major [tile][k][lsum] layout of the other paths.
-#include "su2fft_internal.h"
+#include "su2fft_bf16.h"
 
 namespace su2 {
-
-typedef float floatx4 __attribute__((ext_vector_type(4)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef unsigned short u16x8 __attribute__((ext_vector_type(8)));
-
-__device__ __forceinline__ unsigned short bf16_rne_bits(float f) {
-  unsigned int u = __float_as_uint(f);
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return (unsigned short)(u >> 16);
-}
-__device__ __forceinline__ float bf16_bits_to_f32(unsigned short h) { return __uint_as_float(((unsigned int)h) << 16); }
-
-__device__ __forceinline__ floatx4 mfma_bf16(u16x8 a, u16x8 b, floatx4 c) {
-  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0,
-                                                  0);
-}
-
-// split eight FP32 values into their bf16 hi and lo parts
-__device__ __forceinline__ void split8(const float* v, u16x8& hi, u16x8& lo) {
-#pragma unroll
-  for (int i = 0; i < 8; i++) {
-    const unsigned short h = bf16_rne_bits(v[i]);
-    hi[i] = h;
-    lo[i] = bf16_rne_bits(v[i] - bf16_bits_to_f32(h));
-  }
-}
-
-// eight table words -> hi and lo operands
-__device__ __forceinline__ void unpack8(const unsigned* w, u16x8& hi, u16x8& lo) {
-#pragma unroll
-  for (int i = 0; i < 8; i++) {
-    hi[i] = (unsigned short)(w[i] & 0xffffu);
-    lo[i] = (unsigned short)(w[i] >> 16);
-  }
-}
 
 constexpr int XB_THREADS = 512;
 constexpr int XB_BT = 32;   // inverse: signals per workgroup (64 real columns)
@@ -329,19 +285,17 @@ __device__ __forceinline__ void beta_inverse_bf16x3_body(const cpx<float>* __res
   // at most 16): there they are requested after the products, so that one
   // register set suffices and two workgroups share a CU.
   constexpr bool EARLY = !(LQ == 2 && BT == 16);
-  unsigned aw[2][LQ][8], awn[2][LQ][8];
-  auto fetch_a = [&](unsigned (&dst)[2][LQ][8], int k0) {
+  word4 aw[2][LQ][2], awn[2][LQ][2];
+  auto fetch_a = [&](word4 (&dst)[2][LQ][2], int k0) {
     const int k = k0 + lrow < N ? k0 + lrow : N - 1;
 #pragma unroll
     for (int q = 0; q < 2; q++) {
       const unsigned* trow = tb + (size_t)k * lsum + pi[q].coff + 8 * lg;
 #pragma unroll
       for (int s = 0; s < LQ; s++) {
-#pragma unroll
-        for (int i = 0; i < 8; i++) dst[q][s][i] = 0u;
         if (32 * s < pi[q].L) {  // wave-uniform branch
-#pragma unroll
-          for (int i = 0; i < 8; i++) dst[q][s][i] = trow[32 * s + i];
+          dst[q][s][0] = *reinterpret_cast<const word4*>(trow + 32 * s);
+          dst[q][s][1] = *reinterpret_cast<const word4*>(trow + 32 * s + 4);
         }
       }
     }
@@ -413,7 +367,7 @@ __device__ __forceinline__ void beta_inverse_bf16x3_body(const cpx<float>* __res
 #pragma unroll
         for (int s = 0; s < LQ; s++)
 #pragma unroll
-          for (int i = 0; i < 8; i++) aw[q][s][i] = awn[q][s][i];
+          for (int i = 0; i < 2; i++) aw[q][s][i] = awn[q][s][i];
     }
   }
 }
@@ -456,6 +410,7 @@ static hipError_t set_smem_bf(K kern, size_t smem) {
 
 hipError_t launch_beta_forward_bf16x3(const BetaParams<float>& p, const unsigned* tabf, const cpx<float>* S,
                                       cpx<float>* coeffs, hipStream_t s) {
+  if (beta_bf16_small_forward(p)) return launch_beta_forward_bf16_small(p, tabf, S, coeffs, s);
   const dim3 grid(contraction_grid(p.ntiles - p.tile0, (p.batch + XBF_BT - 1) / XBF_BT, p.paired));
   const int rt = beta_rtmax(p.B);
   hipError_t e;
@@ -474,6 +429,7 @@ hipError_t launch_beta_forward_bf16x3(const BetaParams<float>& p, const unsigned
 
 hipError_t launch_beta_inverse_bf16x3(const BetaParams<float>& p, const unsigned* tabi, const cpx<float>* coeffs,
                                       cpx<float>* S, hipStream_t s) {
+  if (beta_bf16_small_inverse(p)) return launch_beta_inverse_bf16_small(p, tabi, coeffs, S, s);
   // 16-signal tiles for batches of at most 16, and where the widest would
   // leave fewer than 1.5 workgroups per CU (as for the FP32 contractions)
   const bool narrow =

@@ -15,52 +15,9 @@
 // inverse 37 against 22 us).  Plans without the symmetric
 // pair list, and half-spectrum real plans (whose mirrors carry no spectra),
 // take one pair per wave and 8 signals per product.
-#include "su2fft_mfma.h"
+#include "su2fft_beta_small.h"
 
 namespace su2 {
-
-// column cc of a wave's products: which of its MIR pairs, which signal of the
-// tile's BT, and re or im
-template <int MIR>
-struct SmallCols {
-  static constexpr int BT = 8 / MIR;
-  __device__ static __forceinline__ int mir(int cc) { return cc / (2 * BT); }
-  __device__ static __forceinline__ int sig(int cc) { return cc % (2 * BT) / 2; }
-};
-
-// What the kernels need of the wave's pair at list position `at` and of its
-// mirror, and the table column the products read: the pair's own, or its
-// mirror's where the pair is a pad.
-template <class T, int MIR>
-struct SmallPairs {
-  struct Pair {
-    int tm, tn, tl0, L, tsign;
-  };
-  Pair q0, q1;
-  int pos0, pos1, L, lsum;
-  long long tab, itab;  // the column's first value in the row-major and the inverse-layout table
-  __device__ __forceinline__ SmallPairs(const BetaParams<T>& p, int at) {
-    pos0 = at;
-    pos1 = MIR == 2 ? p.ntiles * PT - 1 - at : at;
-    const PairInfo a = p.pairs[pos0], b = p.pairs[pos1];
-    q0 = {a.tm, a.tn, a.tl0, a.L, a.tsign};
-    q1 = {b.tm, b.tn, b.tl0, b.L, b.tsign};
-    if (p.real && mirrored_pair(a.tm, a.tn)) q0.L = q1.L = 0;
-    const bool own = q0.L > 0;
-    // the self-mirror middle tile stores both columns of a couple (2m = 0: the
-    // same values up to sign); reading the first, the second needs its sign
-    if (MIR == 2 && own && b.towner) q1.tsign = (((b.tm - b.tn) / 2) & 1) ? -1 : 1;
-    L = own ? q0.L : q1.L;
-    lsum = own ? a.lsum : b.lsum;
-    tab = own ? a.tab + a.coff : b.tab + b.coff;
-    itab = own ? a.itab : b.itab;
-  }
-  __device__ __forceinline__ Pair pick(int mir) const {
-    if (MIR == 1) return q0;
-    return {mir ? q1.tm : q0.tm, mir ? q1.tn : q0.tn, mir ? q1.tl0 : q0.tl0, mir ? q1.L : q0.L,
-            mir ? q1.tsign : q0.tsign};
-  }
-};
 
 // Forward: fhat(l)_{mn}[b] = sum_k d^l(beta_k) S_k(m, n)[b].  One wave per
 // pair (and mirror): table rows as the A operand, spectra as the B operand,
@@ -78,21 +35,12 @@ __device__ __forceinline__ void store_forward_small(cpx<T>* __restrict__ coeffs,
   const int col = lane & 15, b = b0 + Cols::sig(col);
   const auto q = w.pick(Cols::mir(col));
   if (b >= p.batch) return;
-  const T ts = p.table_signs && q.tsign < 0 ? T(-1) : T(1);
   T* out = reinterpret_cast<T*>(coeffs + coef_offset(p.coff, b, p.ncoef)) + (col & 1);
-  // half-spectrum real plans also write the mirror (-1)^{m-n} conj(fhat) at (-m, -n)
-  const bool mirror = MIR == 1 && p.real && (q.tm != 0 || q.tn != 0);
-  const T sg = ((((q.tm - q.tn) / 2) & 1) ? T(-1) : T(1)) * ((col & 1) ? T(-1) : T(1));
 #pragma unroll
   for (int rt = 0; rt < RT; rt++)
 #pragma unroll
-    for (int r = 0; r < 4; r++) {
-      const int j = RT * acc_row<T>(lane, r) + rt;
-      if (j >= q.L) continue;
-      const T v = ts * acc[rt][r];
-      out[2 * coef_index_of(p.so3, q.tl0 + 2 * j, q.tm, q.tn)] = v;
-      if (mirror) out[2 * coef_index_of(p.so3, q.tl0 + 2 * j, -q.tm, -q.tn)] = sg * v;
-    }
+    for (int r = 0; r < 4; r++)
+      store_coef_small<T, MIR>(out, p, q, RT * acc_row<T>(lane, r) + rt, col & 1, acc[rt][r]);
 }
 
 template <class T, int RT, int MIR>
@@ -108,7 +56,7 @@ __device__ __forceinline__ void beta_forward_small_pair(const cpx<T>* __restrict
   // operand addresses of node lk.  Rows past L read the columns after the
   // pair's (or the padding after the table) and are dropped; signals past the
   // batch read the last one and are dropped likewise.
-  const T* ta = p.tab + w.tab + (long long)lk * w.lsum + RT * lrow;
+  const T* ta = p.tab + w.tab + w.coff + (long long)lk * w.lsum + RT * lrow;
   const int pos = MIR == 2 && Cols::mir(lrow) ? w.pos1 : w.pos0, bs = min(b0 + Cols::sig(lrow), p.batch - 1);
   const T* tb = reinterpret_cast<const T*>(S + (((size_t)(pos / PT) * N + lk) * p.batch + bs) * PT + pos % PT) + (lrow & 1);
   const long long sa = 4LL * w.lsum, sb = 8LL * p.batch * PT;
@@ -248,7 +196,7 @@ __device__ __forceinline__ void beta_forward_mid_body(const cpx<T>* __restrict__
     }
   };
   rowv a[KG];
-  const T* ta = p.tab + w.tab + (long long)lk * w.lsum + RT * lrow;
+  const T* ta = p.tab + w.tab + w.coff + (long long)lk * w.lsum + RT * lrow;
   const long long sa = 4LL * w.lsum;
   auto fetch_a = [&](int c) {
 #pragma unroll
@@ -329,11 +277,6 @@ __global__ __launch_bounds__(MID_THREADS) void beta_forward_mid_kernel(const cpx
 // and written as whole PT-pair rows of S.
 constexpr int SMALL_INV_THREADS = 64 * PT;
 
-template <class T, int BT>
-struct SmallStage {
-  static constexpr int PB = 2 * PT + 2, NRS = BT * PB + 4;
-};
-
 template <class T, int LQ, int MIR>
 __global__ __launch_bounds__(SMALL_INV_THREADS) void beta_inverse_small_kernel(const cpx<T>* __restrict__ coeffs,
                                                                                cpx<T>* __restrict__ S, BetaParams<T> p,
@@ -373,19 +316,10 @@ __global__ __launch_bounds__(SMALL_INV_THREADS) void beta_inverse_small_kernel(c
   {
     const auto q = w.pick(mir);
     const T* c = reinterpret_cast<const T*>(coeffs + coef_offset(p.coff, b0 + min(sig, nb - 1), p.ncoef)) + (lrow & 1);
-    const T sg = ((((q.tm - q.tn) / 2) & 1) ? T(-1) : T(1)) * ((lrow & 1) ? T(-1) : T(1));
 #pragma unroll
     for (int s = 0; s < LQ; s++) {
       bop[s] = T(0);
-      if (s >= G) continue;
-      const int j = 4 * s + lk, tl = q.tl0 + 2 * j;
-      const bool ok = j < q.L && sig < nb;
-      T v = c[ok ? 2 * coef_index_of(p.so3, tl, q.tm, q.tn) : 0];
-      if (MIR == 1 && p.real)  // Hermitian part: (c_{mn} + (-1)^{m-n} conj(c_{-m,-n})) / 2
-        v = T(0.5) * (v + sg * c[ok ? 2 * coef_index_of(p.so3, tl, -q.tm, -q.tn) : 0]);
-      // (2l+1) or 1, times the sign of a mirror column of a stored table
-      const T sc = (p.scale_mode == 0 ? T(tl + 1) : T(1)) * (p.table_signs && q.tsign < 0 ? T(-1) : T(1));
-      bop[s] = ok ? v * sc : T(0);
+      if (s < G) bop[s] = load_coef_small<T, MIR>(c, p, q, 4 * s + lk, lrow & 1, sig < nb);
     }
   }
 
@@ -399,41 +333,12 @@ __global__ __launch_bounds__(SMALL_INV_THREADS) void beta_inverse_small_kernel(c
       if (s < G) acc = mfma16x16x4(av[s], bop[s], acc);
     if (kb + 1 < kb1) fetch();  // next block's values, in flight during the stores
     // two stage buffers in turn: one barrier per block
-    T* stage = stages[kb & 1];
 #pragma unroll
     for (int r = 0; r < 4; r++) mine[(kb & 1) * MIR * 16 * ST::NRS + acc_row<T>(lane, r) * ST::NRS] = acc[r];
     __syncthreads();
-    // rows (node, signal) of PT pairs, 16 bytes per store
-    constexpr int VC = 16 / (int)sizeof(cpx<T>), VPR = PT / VC;
-    typedef T vec16 __attribute__((ext_vector_type(16 / sizeof(T))));
-    const int mirs = MIR == 2 && p.ntiles - 1 - tile == tile ? 1 : MIR;  // a self-mirror tile once
-    for (int v = tid; v < mirs * 16 * BT * VPR; v += SMALL_INV_THREADS) {
-      const int pv = v % VPR, bb = v / VPR % BT, kk = v / (VPR * BT) % 16, h = v / (VPR * BT * 16);
-      const int k = 16 * kb + kk;
-      if (k >= N || bb >= nb) continue;
-      const T* src = stage + (h * 16 + kk) * ST::NRS + bb * ST::PB + 2 * pv * VC;
-      vec16 x;
-#pragma unroll
-      for (int e = 0; e < 2 * VC; e++) x[e] = src[e];
-      const int t = h ? p.ntiles - 1 - tile : tile;
-      *reinterpret_cast<vec16*>(S + (((size_t)t * N + k) * p.batch + b0 + bb) * PT + pv * VC) = x;
-    }
+    store_rows_small<T, MIR, SMALL_INV_THREADS>(S, p, stages[kb & 1], tile, kb, b0, nb, tid);
   }
 }
-
-// pairs of a wave: a pair and its mirror where the plan's list is
-// point-symmetric and every pair carries spectra
-template <class T>
-static bool small_mirrored(const BetaParams<T>& p) { return p.sym && !p.real; }
-
-// pair tiles (with their mirrors) of a launch
-template <class T>
-static long long small_units(const BetaParams<T>& p) {
-  return small_mirrored(p) ? (p.ntiles + 1) / 2 : p.ntiles - p.tile0;
-}
-// enough tiles that workgroups of one tile each reach three of four CUs
-template <class T>
-static bool small_fills(const BetaParams<T>& p) { return 4 * small_units(p) >= 3LL * device_cus(); }
 
 // Forward: these kernels instead of the tile kernel where its grid of tiles and
 // 16- or 32-signal groups leaves CUs idle or columns empty, i.e. by signals
@@ -511,18 +416,7 @@ static hipError_t launch_inverse_small_lq(const BetaParams<T>& p, const cpx<T>* 
   constexpr int BT = SmallCols<MIR>::BT;
   const int ntl = MIR == 2 ? (p.ntiles + 1) / 2 : p.ntiles - p.tile0, nbt = (p.batch + BT - 1) / BT;
   const int NB = (p.N + 15) / 16;
-  // node blocks per workgroup: the fewest block times, counting the coefficient
-  // gather at a workgroup's start as two, with two workgroups per CU at a time
-  const long long slots = 2LL * device_cus(), have = (long long)ntl * nbt;
-  int blocks = NB;
-  long long best = 0;
-  for (int b = NB; b >= 1; b--) {
-    const long long nsplit = (NB + b - 1) / b, cost = (have * nsplit + slots - 1) / slots * (b + 2);
-    if (b == NB || cost < best) {
-      best = cost;
-      blocks = b;
-    }
-  }
+  const int blocks = small_inverse_blocks((long long)ntl * nbt, NB);
   const dim3 grid(contraction_grid(ntl, (NB + blocks - 1) / blocks * nbt)), block(SMALL_INV_THREADS);
   hipLaunchKernelGGL((beta_inverse_small_kernel<T, LQ, MIR>), grid, block, 0, s, coeffs, S, p, ntl, blocks);
   return hipGetLastError();

@@ -328,6 +328,14 @@ hipError_t launch_beta_forward_bf16x3(const BetaParams<float>& p, const unsigned
                                       cpx<float>* coeffs, hipStream_t s);
 hipError_t launch_beta_inverse_bf16x3(const BetaParams<float>& p, const unsigned* tabi, const cpx<float>* coeffs,
                                       cpx<float>* S, hipStream_t s);
+// the same for small batches (su2fft_beta_bf16_small.hip): whether the streaming
+// kernels take a call, and their launches
+bool beta_bf16_small_forward(const BetaParams<float>& p);
+bool beta_bf16_small_inverse(const BetaParams<float>& p);
+hipError_t launch_beta_forward_bf16_small(const BetaParams<float>& p, const unsigned* tabf, const cpx<float>* S,
+                                          cpx<float>* coeffs, hipStream_t s);
+hipError_t launch_beta_inverse_bf16_small(const BetaParams<float>& p, const unsigned* tabi, const cpx<float>* coeffs,
+                                          cpx<float>* S, hipStream_t s);
 // N = 256 rings in FP32 in one pass, four workgroups per ring, two per CU
 // (forward: samples -> S; inverse / adjoint: S -> samples)
 hipError_t launch_ring_sliced4(bool forward, const FastRingParams<float>& p, const cpx<float>* in, cpx<float>* out,
