@@ -342,32 +342,44 @@ __global__ __launch_bounds__(SMALL_INV_THREADS) void beta_inverse_small_kernel(c
 
 // Forward: these kernels instead of the tile kernel where its grid of tiles and
 // 16- or 32-signal groups leaves CUs idle or columns empty, i.e. by signals
-// times tiles; with a tile per CU or more, by signals.  Tile kernel -> these, us:
-// FP32 B = 24, 48 signals 11.5 -> 11.1, 64 signals 14.4 -> 14.9; B = 36, 17 signals
-// 21 -> 13, 48 signals 26 -> 34; B = 64, 1 signal 42 -> 14, 8 signals 45 -> 30,
-// 12 signals 46 -> 41, 16 signals 47 -> 53; B = 72, 16 signals 89 -> 62; B = 128,
-// 1 signal 371 -> 123.  FP64 B = 36, 24 signals 38 -> 23; B = 64, 1 signal
-// 57 -> 15, 12 signals 60 -> 57, 16 signals 69 -> 90; B = 128, 1 signal 795 -> 241 (the
-// table alone takes 133 at the copy rate).
+// times tiles; with a tile per CU or more, by signals, two groups of 4 (three
+// with the long columns of B > 64 in FP32).  Whole calls on inputs not in the
+// caches, tile kernel -> these, us:
+// FP32 B = 24, 32 signals 23.9 -> 20.6, 52 signals 30.3 -> 30.5; B = 32, 16 signals
+// 30.3 -> 26.2, 28 signals 37.6 -> 38.5; B = 48, 8 signals 48 -> 43, 12 signals
+// 62 -> 65; B = 64, 1 signal 56 -> 29, 8 signals 89 -> 76, 12 signals 110.4 -> 110.5;
+// B = 72, 12 signals 236 -> 210; B = 128, 8 signals 917 -> 806.
+// FP64 B = 32, 24 signals 64.3 -> 63.6, 30 signals 69 -> 73; B = 48, 16 signals
+// 143 -> 137; B = 54, 12 signals 197.1 -> 196.5; SO(3) B = 64 (whole row tiles),
+// 4 signals 94 -> 69, 12 signals 191 -> 197; B = 64, 4 signals 115 -> 104,
+// 8 signals 170 -> 166, 9 signals 193 -> 206; B = 96, 4 signals 557 -> 375.
 template <class T>
 bool beta_small_forward(const BetaParams<T>& p) {
-  if (small_fills(p)) return p.batch <= (p.B > 64 ? 16 : 12);
-  return p.batch * small_units(p) <= (sizeof(T) == 4 ? 1900 : 2700);
+  if (small_fills(p)) return p.batch <= (sizeof(T) == 4 && p.B > 64 ? 12 : 8);
+  if (sizeof(T) == 4 || beta_rtmax(p.B) == 1) return p.batch * small_units(p) <= 1600;
+  return p.batch * small_units(p) <= (p.B <= 54 ? 2300 : 1200);
 }
 
 // Inverse: likewise (its tile kernel also gathers the coefficients through
-// eight barriers); up to 8 degrees the tile kernel is as fast and smaller.  Tile
-// kernel -> this, us: FP32 B = 32, 48 signals 15.8 -> 15.0, 64 signals 17.7 -> 18.5;
-// B = 36, 17 signals 17.5 -> 12; B = 64, 1 signal 27 -> 13, 12 signals 33.9 -> 33.2,
-// 24 signals 54.7 -> 55.9; B = 96, 12 signals 171 -> 143.  FP64 B = 48, 12 signals
-// 34 -> 22; B = 64, 1 signal 53 -> 19, 9 signals 56 -> 46, 12 signals 62 -> 68; B = 96,
-// 12 signals 354 -> 304.
+// eight barriers); up to 8 degrees the tile kernel is as fast and smaller.
+// FP32 B = 24, 52 signals 30.0 -> 30.4; B = 32, 16 signals 28.5 -> 25.3, 40 signals
+// 47.6 -> 46.8, 60 signals 58 -> 59; B = 36, 44 signals 73.1 -> 72.6; B = 48, 12 signals
+// 60 -> 55, 24 signals 110 -> 108; B = 64, 8 signals 77 -> 74, 9 signals 88 -> 94;
+// B = 72, 12 signals 257 -> 229; B = 96, 8 signals 469 -> 405.
+// FP64 B = 24, 72 signals 55.4 -> 54.4; B = 32, 32 signals 73 -> 69, 45 signals
+// 105 -> 110; B = 48, 20 signals 209 -> 197; SO(3) B = 64, 4 signals 84 -> 64,
+// 12 signals 172 -> 177; B = 64, 8 signals 166 -> 156, 9 signals 197 -> 205;
+// half-spectrum B = 64, 8 signals 106 -> 107; B = 96, 4 signals 586 -> 421.
 template <class T>
 bool beta_small_inverse(const BetaParams<T>& p) {
   const int lq = beta_lq(p.B);
   if (lq == 2) return false;
-  if (lq == 16) return p.batch <= 16;
-  return p.batch * small_units(p) <= (sizeof(T) == 4 ? 4000 : 2900);
+  if (small_fills(p)) {
+    if (sizeof(T) == 4) return p.batch <= (p.B > 64 ? 12 : 8);
+    return p.batch <= (small_mirrored(p) ? 8 : 4);
+  }
+  if (sizeof(T) == 4) return p.batch <= 40 && p.batch * small_units(p) <= 3600;
+  return p.batch * small_units(p) <= (lq == 4 ? 2550 : p.B <= 54 ? 2900 : 1200);
 }
 
 // Forward with the spectra through LDS: where the lines of S that the
