@@ -154,7 +154,8 @@ def shifted_depth1_flops(B: int, batch: int) -> float:
 
 # sources of the kernels the B = 64 chain launches (the counter summaries in
 # profiles/ are valid only for the digest they were taken at)
-MEASURED_SOURCES = ["su2fft_internal.h", "su2fft_ring_fast.hip", "su2fft_beta.hip", "su2fft_beta_bf16.hip"]
+MEASURED_SOURCES = ["su2fft_internal.h", "su2fft_mfma.h", "su2fft_bf16.h", "su2fft_ring_fast.hip", "su2fft_beta.hip",
+                    "su2fft_beta_bf16.hip"]
 
 
 def source_digest() -> str:
