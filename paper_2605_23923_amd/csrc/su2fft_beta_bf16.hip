@@ -15,17 +15,19 @@ constexpr int XBF_BT = 16;  // forward: signals per workgroup (a 32-node S chunk
 constexpr int XB_KC = 32;   // nodes per chunk = K of one matrix instruction
 
 // Forward.  One workgroup per (pair tile, signal tile), in the order of
-// contraction_slot; wave w owns pairs w and w + 8.
+// contraction_slot; wave w owns pairs w and w + 8 (or pair w alone).
 // S streams through LDS in chunks of 32 nodes with register prefetch; the
 // table operand is read straight from the node-interleaved layout.
 constexpr size_t XBF_SMEM = (size_t)XB_KC * (XBF_BT * (2 * PT + 2) + 16) * sizeof(float);
 constexpr size_t XBI_SMEM = (size_t)16 * XB_BT * (2 * PT + 2) * sizeof(float);
 
-// EARLY: the table operands of a chunk are requested together at its start.
-// Measured at four row tiles (B = 128 batch 16: 0.495 -> 0.476 ms); at two
-// (B = 64) the requests inside the tile loop are 1-2 % faster.  The
-// work-list kernel of mixed plans, with less register room, keeps them there.
-template <int RTMAX, bool EARLY = (RTMAX >= 4)>
+// NP: pairs per wave.  With four row tiles two pairs take 234 registers, one
+// 8-wave workgroup per CU; one pair takes 108, so 16 waves share the CU and
+// cover each other's loads: B = 72, 32 signals 168 -> 140 us; B = 96, 16 signals
+// 194 -> 166; B = 128, 16 signals 437 -> 404, 24 signals 732 -> 659.  (With a chunk's
+// table operands requested together at its start, which two pairs gained
+// from, one pair spills at 128 registers: B = 128, 16 signals 438 us.)
+template <int RTMAX, int NP = 2>
 __device__ __forceinline__ void beta_forward_bf16x3_body(const cpx<float>* __restrict__ S,
                                                          cpx<float>* __restrict__ coeffs, const BetaParams<float>& p,
                                                          const unsigned* __restrict__ tabf, int tile, int bt,
@@ -35,8 +37,9 @@ __device__ __forceinline__ void beta_forward_bf16x3_body(const cpx<float>* __res
   constexpr int PK = BT * PB + 16;
   constexpr int VC = 2;                         // complex values per 16-byte load
   constexpr int SV = KC * BT * PT / VC;
-  constexpr int SPT = SV / XB_THREADS;
-  static_assert(SV % XB_THREADS == 0, "chunk split");
+  constexpr int NT = 64 * PT / NP;  // threads: NP pairs per wave
+  constexpr int SPT = SV / NT;
+  static_assert(SV % NT == 0, "chunk split");
   float* sS = reinterpret_cast<float*>(smem);
 
   const int b0 = bt * BT;
@@ -52,16 +55,16 @@ __device__ __forceinline__ void beta_forward_bf16x3_body(const cpx<float>* __res
   // at (tab / N) * NB8 * 8, tab being the tile offset in the [k][lsum] layout
   const unsigned* tb = tabf + (p0.tab / N) * (long long)NB8 * 8;
 
-  PairInfo pi[2];
+  PairInfo pi[NP];
 #pragma unroll
-  for (int i = 0; i < 2; i++) {
+  for (int i = 0; i < NP; i++) {
     pi[i] = p.pairs[tile * PT + wave + 8 * i];
     if (p.real && mirrored_pair(pi[i].tm, pi[i].tn)) pi[i].L = 0;  // its coefficients come from the mirror
   }
 
-  floatx4 acc[2][RTMAX][CT];
+  floatx4 acc[NP][RTMAX][CT];
 #pragma unroll
-  for (int i = 0; i < 2; i++)
+  for (int i = 0; i < NP; i++)
 #pragma unroll
     for (int rt = 0; rt < RTMAX; rt++)
 #pragma unroll
@@ -70,14 +73,14 @@ __device__ __forceinline__ void beta_forward_bf16x3_body(const cpx<float>* __res
   // HALF: the next chunk's first half is requested before the current
   // chunk's products and its second half after them, so that the prefetch
   // holds half the registers
-  constexpr bool HALF = RTMAX == 2 && !EARLY;
+  constexpr bool HALF = RTMAX == 2;
   constexpr int SH = HALF ? SPT / 2 : SPT;
   float4 sreg[SH];
   auto fetch = [&](int k0, int h) {
 #pragma unroll
     for (int ii = 0; ii < SH; ii++) {
       const int i = h * SH + ii;
-      const int v = tid + XB_THREADS * i;
+      const int v = tid + NT * i;
       const int kk = v / (BT * PT / VC), rem = v - kk * (BT * PT / VC);
       const int bb = rem / (PT / VC), pv = rem - bb * (PT / VC);
       const int k = k0 + kk;
@@ -91,7 +94,7 @@ __device__ __forceinline__ void beta_forward_bf16x3_body(const cpx<float>* __res
 #pragma unroll
     for (int ii = 0; ii < SH; ii++) {
       const int i = h * SH + ii;
-      const int v = tid + XB_THREADS * i;
+      const int v = tid + NT * i;
       const int kk = v / (BT * PT / VC), rem = v - kk * (BT * PT / VC);
       const int bb = rem / (PT / VC), pv = rem - bb * (PT / VC);
       float* d = sS + kk * PK + bb * PB + 2 * pv * VC;
@@ -110,26 +113,8 @@ __device__ __forceinline__ void beta_forward_bf16x3_body(const cpx<float>* __res
     __syncthreads();
     if (c + 1 < nchunk) fetch((c + 1) * KC, 0);
     const int kb = c * (KC / 8) + lg;  // this lane's group of 8 nodes
-    // the chunk's table operands of both pairs, requested together before
-    // any of them is used (an index out of range reads the table's first
-    // row and is masked to zero), so their latencies overlap
-    uint4 tw[2][RTMAX][2];
-    bool tok[2][RTMAX];
 #pragma unroll
-    for (int i = 0; i < 2; i++)
-#pragma unroll
-      for (int rt = 0; rt < RTMAX; rt++) {
-        const int l = rt * 16 + lrow;
-        tok[i][rt] = l < pi[i].L && kb < NB8;
-        if constexpr (EARLY) {
-          const uint4* src = reinterpret_cast<const uint4*>(
-              tok[i][rt] ? tb + ((size_t)kb * lsum + pi[i].coff + l) * 8 : tabf);
-          tw[i][rt][0] = src[0];
-          tw[i][rt][1] = src[1];
-        }
-      }
-#pragma unroll
-    for (int i = 0; i < 2; i++) {
+    for (int i = 0; i < NP; i++) {
       const int L = pi[i].L;
       if (L == 0) continue;
       const int pp = wave + 8 * i;
@@ -147,14 +132,10 @@ __device__ __forceinline__ void beta_forward_bf16x3_body(const cpx<float>* __res
       for (int rt = 0; rt < RTMAX; rt++) {
         if (rt * 16 < L) {
           u16x8 ahi, alo;
-          if (tok[i][rt]) {
-            if constexpr (!EARLY) {
-              const uint4* src =
-                  reinterpret_cast<const uint4*>(tb + ((size_t)kb * lsum + pi[i].coff + rt * 16 + lrow) * 8);
-              tw[i][rt][0] = src[0];
-              tw[i][rt][1] = src[1];
-            }
-            const uint4 w0 = tw[i][rt][0], w1 = tw[i][rt][1];
+          const int l = rt * 16 + lrow;
+          if (l < L && kb < NB8) {
+            const uint4* src = reinterpret_cast<const uint4*>(tb + ((size_t)kb * lsum + pi[i].coff + l) * 8);
+            const uint4 w0 = src[0], w1 = src[1];
             const unsigned w[8] = {w0.x, w0.y, w0.z, w0.w, w1.x, w1.y, w1.z, w1.w};
             unpack8(w, ahi, alo);
           } else {
@@ -182,7 +163,7 @@ __device__ __forceinline__ void beta_forward_bf16x3_body(const cpx<float>* __res
 
   // epilogue: the coefficients leave through LDS (CoefRound), 8 degrees of
   // all 16 pairs per round
-  typedef CoefRound<float, BT, XB_THREADS> CR;
+  typedef CoefRound<float, BT, NT> CR;
   static_assert(CR::ELEMS * sizeof(float) <= XBF_SMEM, "coefficient rounds fit");
   float* cst = reinterpret_cast<float*>(smem);
 #pragma unroll
@@ -190,7 +171,7 @@ __device__ __forceinline__ void beta_forward_bf16x3_body(const cpx<float>* __res
     const int rt = j0 / 16, r0 = j0 % 16;
     __syncthreads();  // LDS free (main loop, or the previous round's reads)
 #pragma unroll
-    for (int h = 0; h < 2; h++) {
+    for (int h = 0; h < NP; h++) {
       if (rt * 16 < pi[h].L) {
 #pragma unroll
         for (int ct = 0; ct < CT; ct++)
@@ -207,14 +188,19 @@ __device__ __forceinline__ void beta_forward_bf16x3_body(const cpx<float>* __res
 }
 
 template <int RTMAX>
-__global__ __launch_bounds__(XB_THREADS, RTMAX == 2 ? 4 : 1) void beta_forward_bf16x3_kernel(const cpx<float>* __restrict__ S,
-                                                                         cpx<float>* __restrict__ coeffs,
-                                                                         BetaParams<float> p,
-                                                                         const unsigned* __restrict__ tabf) {
+constexpr int bf16_forward_pairs() { return RTMAX >= 4 ? 1 : 2; }  // per wave
+
+// 128 registers, two workgroups per CU; with one row tile the compiler takes 129
+// unbidden: B = 32, 256 signals 90 -> 62 us, B = 24, 150 signals 30.5 -> 25.2
+template <int RTMAX>
+__global__ __launch_bounds__(64 * PT / bf16_forward_pairs<RTMAX>(), RTMAX <= 2 ? 4 : 1) void beta_forward_bf16x3_kernel(
+    const cpx<float>* __restrict__ S, cpx<float>* __restrict__ coeffs, BetaParams<float> p,
+    const unsigned* __restrict__ tabf) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   const TileSlot sl = contraction_slot(blockIdx.x, p.ntiles - p.tile0, (p.batch + XBF_BT - 1) / XBF_BT, p.paired);
   if (!sl.valid) return;
-  beta_forward_bf16x3_body<RTMAX>(S, coeffs, p, tabf, p.tile0 + sl.tile, sl.bt, smem_raw, threadIdx.x);
+  beta_forward_bf16x3_body<RTMAX, bf16_forward_pairs<RTMAX>()>(S, coeffs, p, tabf, p.tile0 + sl.tile, sl.bt, smem_raw,
+                                                               threadIdx.x);
 }
 
 // Inverse.  One workgroup per (pair tile, signal tile), in the order of
@@ -417,7 +403,8 @@ hipError_t launch_beta_forward_bf16x3(const BetaParams<float>& p, const unsigned
 #define SU2_XBF_CASE(R)                                                                                           \
   if (rt == R) {                                                                                                  \
     if ((e = set_smem_bf(beta_forward_bf16x3_kernel<R>, XBF_SMEM)) != hipSuccess) return e;                       \
-    hipLaunchKernelGGL((beta_forward_bf16x3_kernel<R>), grid, dim3(XB_THREADS), XBF_SMEM, s, S, coeffs, p, tabf); \
+    hipLaunchKernelGGL((beta_forward_bf16x3_kernel<R>), grid, dim3(64 * PT / bf16_forward_pairs<R>()), XBF_SMEM, s, S, \
+                       coeffs, p, tabf);                                                                          \
     return hipGetLastError();                                                                                     \
   }
   SU2_XBF_CASE(1)

@@ -261,16 +261,18 @@ __global__ __launch_bounds__(BS_THREADS) void beta_inverse_bf16_small_kernel(con
 // Forward: this kernel instead of the tile kernel where its grid of tiles and
 // 16-signal groups leaves CUs idle or columns empty: by signals times tiles, further
 // with one row tile of degrees (B <= 32); with a tile per CU or more, by signals.
-// Whole calls on inputs not in the caches, tile kernel -> this, us: B = 24,
-// 100 signals 54 -> 48; B = 32, 60 signals 67 -> 62; B = 36, 20 signals 44.5 -> 43.3
-// (the contraction alone at 48 signals 23 -> 29); B = 48, 12 signals 58.8 -> 57.5;
-// B = 54, 8 signals 71 -> 68 (alone at 12 signals 25.4 -> 27.0); B = 64, 4 signals
-// 50 -> 40, 8 signals 76 -> 73 (alone at 9 signals 30.9 -> 32.0); B = 72, 12 signals
-// 237 -> 211.  Alone: B = 96, 12 signals 169 -> 133; B = 128, 1 signal 297 -> 113 (the
-// table takes 68 at the copy rate), 12 signals 400 -> 358, 16 signals 437 -> 460.
+// Whole calls on inputs not in the caches, tile kernel -> this, us: B = 32,
+// 32 signals 38.7 -> 35.2 (the contraction alone at 64 signals, the last of this
+// kernel's gain: 24.9 -> 19.4 before the tile kernel ran two workgroups per CU);
+// B = 36, 20 signals 44.5 -> 43.3 (alone at 48 signals 23 -> 29); B = 48, 12 signals
+// 58.8 -> 57.5; B = 54, 8 signals 71 -> 68 (alone at 12 signals 25.4 -> 27.0);
+// B = 64, 4 signals 50 -> 40, 8 signals 76 -> 73 (alone at 9 signals 30.9 -> 32.0);
+// alone: B = 72, 12 signals 73 -> 48 (16 signals 65 on the tile kernel); B = 96,
+// 12 signals 169 -> 133; B = 128, 1 signal 297 -> 113 (the table takes 68 at the copy
+// rate), 8 signals 341 -> 254, 12 signals 360 (tile kernel at 13: 361).
 bool beta_bf16_small_forward(const BetaParams<float>& p) {
-  if (small_fills(p)) return p.batch <= (p.B > 64 ? 12 : 8);
-  return p.batch * small_units(p) <= (beta_rtmax(p.B) == 1 ? 4000 : 1800);
+  if (small_fills(p)) return p.batch <= (p.B > 64 && p.B <= 108 ? 12 : 8);
+  return p.batch * small_units(p) <= (beta_rtmax(p.B) == 1 ? 2500 : 1800);
 }
 
 // Inverse: likewise; further where the 32-degree products of the tile kernel

@@ -38,3 +38,18 @@ def test_small_bf16_batches_bitwise_equal_tile_kernels(B, kind, monkeypatch):
         plan.close()
         for name, a, w in zip(("forward", "inverse", "adjoint"), got, want):
             assert np.array_equal(a, w[at]), (batch, name)
+
+
+@pytest.mark.parametrize("B,batch", [(24, 130), (72, 17), (81, 33), (128, 13)])
+def test_bf16_forward_tiles_bitwise_equal_work_lists(B, batch, monkeypatch):
+    """The single-plan forward tile kernels at one row tile (two workgroups per
+    CU) and four (one pair per wave), whole and partial 16-signal tiles."""
+    monkeypatch.setenv("SU2_AUTOTUNE", "0")
+    big, plan = su2.MixedPlan([B] * batch, "c64_bf16x3"), su2.Plan(B, batch, "c64_bf16x3")
+    g = torch.Generator(device="cuda").manual_seed(B)
+    x = torch.randn(*plan.sample_shape, 2, generator=g, device="cuda")
+    x = torch.view_as_complex(x)
+    want = big.forward(x.view(-1)).view(plan.coeff_shape)
+    assert torch.equal(plan.forward(x), want)
+    big.close()
+    plan.close()
