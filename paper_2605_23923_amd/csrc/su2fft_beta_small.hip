@@ -56,6 +56,7 @@ __device__ __forceinline__ void beta_forward_small_pair(const cpx<T>* __restrict
   // operand addresses of node lk.  Rows past L read the columns after the
   // pair's (or the padding after the table) and are dropped; signals past the
   // batch read the last one and are dropped likewise.
+  static_assert(16 * RT <= TABLE_PAD && 15 * RT + 4 <= TABLE_PAD, "a three-value load may take four");
   const T* ta = p.tab + w.tab + w.coff + (long long)lk * w.lsum + RT * lrow;
   const int pos = MIR == 2 && Cols::mir(lrow) ? w.pos1 : w.pos0, bs = min(b0 + Cols::sig(lrow), p.batch - 1);
   const T* tb = reinterpret_cast<const T*>(S + (((size_t)(pos / PT) * N + lk) * p.batch + bs) * PT + pos % PT) + (lrow & 1);
@@ -195,6 +196,9 @@ __device__ __forceinline__ void beta_forward_mid_body(const cpx<T>* __restrict__
         for (int e = 0; e < 2 * MS::VC; e++) d[mir * MS::HALF + (kk * BT + bb) * MS::PB + 2 * pv * MS::VC + e] = sv[i][e];
     }
   };
+  // RT is the tile's: a pair with fewer row tiles reads the columns after its
+  // own, or the padding after the table, and drops the rows
+  static_assert(16 * RT <= TABLE_PAD && 15 * RT + 4 <= TABLE_PAD, "a three-value load may take four");
   rowv a[KG];
   const T* ta = p.tab + w.tab + w.coff + (long long)lk * w.lsum + RT * lrow;
   const long long sa = 4LL * w.lsum;

@@ -540,11 +540,9 @@ su2_status_t build_plan(su2_plan_s* pl) {
   // shifted-recurrence contraction use them (a few MB)
   if ((e = upload_otf_scalars(pl, beta)) != hipSuccess) return hip_fail(e);
   if (!pl->otf) {
-    // tables are padded by 16 zeros: the contraction kernels read whole
-    // 16-byte vectors, and up to 15 elements past a pair's row segment
-    // (multiplied by zero operands, or in result rows that are dropped)
-    if ((e = pl->alloc((void**)&pl->d_tab64, sizeof(double) * ((size_t)tab + 16))) != hipSuccess) return hip_fail(e);
-    if ((e = hipMemset(pl->d_tab64 + tab, 0, 16 * sizeof(double))) != hipSuccess) return hip_fail(e);
+    if ((e = pl->alloc((void**)&pl->d_tab64, sizeof(double) * ((size_t)tab + TABLE_PAD))) != hipSuccess)
+      return hip_fail(e);
+    if ((e = hipMemset(pl->d_tab64 + tab, 0, sizeof(double) * TABLE_PAD)) != hipSuccess) return hip_fail(e);
     if ((e = launch_dtable(B, N, pl->P_pad, pl->d_pairs, d_beta, pl->d_tab64, 0)) != hipSuccess) return hip_fail(e);
     // the inverse-layout copy read by the inverse and adjoint contractions
     if (pl->dtype == SU2_C128) {
@@ -562,14 +560,15 @@ su2_status_t build_plan(su2_plan_s* pl) {
   if (pl->otf) {
     // no stored table
   } else if (pl->dtype == SU2_C64) {
-    if ((e = pl->alloc((void**)&pl->d_tab32, sizeof(float) * (size_t)tab + 64)) != hipSuccess) return hip_fail(e);
-    if ((e = hipMemset(pl->d_tab32 + tab, 0, 64)) != hipSuccess) return hip_fail(e);
+    if ((e = pl->alloc((void**)&pl->d_tab32, sizeof(float) * ((size_t)tab + TABLE_PAD))) != hipSuccess)
+      return hip_fail(e);
+    if ((e = hipMemset(pl->d_tab32 + tab, 0, sizeof(float) * TABLE_PAD)) != hipSuccess) return hip_fail(e);
     if ((e = launch_round_table_f32(tab, pl->d_tab64, pl->d_tab32, 0)) != hipSuccess) return hip_fail(e);
   } else if (pl->dtype == SU2_C64_BF16X3) {
-    // 256 bytes of zeros after the last block: the split inverse reads up to
-    // 31 words past a pair's row segment (against zero operands)
-    if ((e = pl->alloc((void**)&pl->d_tabbf, sizeof(bf16x2_t) * (size_t)tab + 256)) != hipSuccess) return hip_fail(e);
-    if ((e = hipMemset(pl->d_tabbf + tab, 0, 256)) != hipSuccess) return hip_fail(e);
+    // the split inverse reads up to 31 words past a pair's row segment (against zero operands)
+    if ((e = pl->alloc((void**)&pl->d_tabbf, sizeof(bf16x2_t) * ((size_t)tab + TABLE_PAD))) != hipSuccess)
+      return hip_fail(e);
+    if ((e = hipMemset(pl->d_tabbf + tab, 0, sizeof(bf16x2_t) * TABLE_PAD)) != hipSuccess) return hip_fail(e);
     if ((e = launch_split_table_bf16(tab, pl->d_tab64, pl->d_tabbf, 0)) != hipSuccess) return hip_fail(e);
     const long long fwd_words = tab / N * (long long)((N + 7) / 8) * 8;
     if ((e = pl->alloc((void**)&pl->d_tabbf_fwd, sizeof(unsigned) * (size_t)fwd_words + 64)) != hipSuccess)

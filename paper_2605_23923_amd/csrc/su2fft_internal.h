@@ -62,6 +62,13 @@ struct PairInfo {
   int towner;     // 1: the column was generated for this pair; 0: it is its mirror's
 };
 
+// Zeros after the last block of a stored table (elements).  The contraction
+// kernels read whole 16-byte vectors, and the streaming forward reads up to
+// four row tiles of 16 degrees from a pair's first column, however few degrees
+// the pair has; both may run past the last block's last row.  The values meet
+// zero operands or result rows that are dropped.
+constexpr int TABLE_PAD = 64;
+
 // Inverse-layout table: the values one wave of the inverse contraction loads
 // as matrix-core A operands, in lane order.  For a pair with L degrees,
 // S = ceil(L / 4) groups of 4 degrees and NB = ceil(N / 16) blocks of 16
