@@ -95,6 +95,12 @@ struct RadixRingParams {
   int so3;                  // SO(3) plan: integer n only, no half-bin shift on any q
   int real_io;              // real samples: the forward reads reals, the inverse writes the real part
 };
+// a group of a mixed plan whose rings run in one launch with other groups'
+template <class T>
+struct RadixListGroup {
+  RadixRingParams<T> p[3];  // forward, inverse, adjoint
+  cpx<T>* S;
+};
 
 // start of signal b's samples: an explicit offset table (batches of signals with
 // different bandlimits share one buffer) or the dense stride N^3
@@ -303,6 +309,16 @@ template <class T>
 hipError_t launch_ring_forward_radix(const RadixRingParams<T>& p, const cpx<T>* samples, cpx<T>* S, hipStream_t s);
 template <class T>
 hipError_t launch_ring_inverse_radix(const RadixRingParams<T>& p, const cpx<T>* S, cpx<T>* samples, hipStream_t s);
+// mixed-radix rings of several groups in one launch: workgroups of a group's
+// rings (0: the length is not one of the list's), LDS bytes of a length, and
+// the launch over n items (group, workgroup of the group)
+template <class T>
+int radix_list_blocks(int N, long long rings);
+template <class T>
+size_t radix_list_smem(int N);
+template <class T>
+hipError_t launch_radix_list(bool forward, int dir, const int2* items, int n, size_t smem,
+                             const RadixListGroup<T>* groups, const cpx<T>* in, cpx<T>* out, hipStream_t s);
 template <class T>
 hipError_t launch_beta_forward(const BetaParams<T>& p, const cpx<T>* S, cpx<T>* coeffs, hipStream_t s);
 template <class T>

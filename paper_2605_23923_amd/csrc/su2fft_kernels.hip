@@ -9,7 +9,8 @@
 // tile) contraction tasks split by contraction shape class and tile width, each launch
 // calling the same kernel bodies as the single-B launches (so every signal's
 // result is bit-identical to a single-B plan's); the rings of mixed-radix and
-// N = 256 groups run the single-B plan's own kernels beside the work lists.  Tasks
+// N = 256 groups run the single-B plan's own kernels beside the work lists, small
+// mixed-radix groups together in one launch.  Tasks
 // are ordered by decreasing cost and taken in a static stride by a grid of
 // `knob x CUs` workgroups, or (knob 0) one workgroup per task; the knob of
 // each kernel is chosen by timing the candidates at plan creation
@@ -206,9 +207,16 @@ struct MixedState {
   su2::WorkItem* d_betai = nullptr;
   int n_ringf = 0, n_betaf = 0, n_betai = 0;
   // groups whose rings run the single-B plan's own launches instead of a work
-  // list: the mixed-radix kernels, and N = 256 (one-pass sliced in FP32,
-  // two-pass in FP64)
+  // list: the mixed-radix kernels (but for the small groups below), and
+  // N = 256 (one-pass sliced in FP32, two-pass in FP64)
   std::vector<int> dedicated;
+  // mixed-radix groups too small to fill the chip, run in one launch together
+  // (not in `dedicated`)
+  void* d_radix_groups = nullptr;  // RadixListGroup<T>[groups]
+  int2* d_radix = nullptr;         // (group, workgroup of the group)
+  int n_radix = 0;
+  size_t smem_radix = 0;
+  bool ringf_longer = false;       // the register-resident rings are at least half of the ring work
   // the contraction lists in runs of one shape class (forward: row tiles;
   // inverse: degrees per group), largest class first: a run is one launch of
   // the kernel built for exactly that class, so that the small bandlimits
@@ -234,7 +242,7 @@ struct MixedState {
   std::vector<int> narrow_f, narrow_i;
   int max_betaf = 0, max_betai = 0;  // work-list capacities (every group in 16-signal tiles)
   hipStream_t cap = nullptr;          // capture stream
-  hipStream_t side = nullptr;         // second branch: mixed-radix and N = 256 rings beside the fast ones
+  hipStream_t side = nullptr;         // second branch
   hipEvent_t fork = nullptr, join = nullptr;
   std::vector<MixedGraph> graphs;
   std::vector<MixedGraph> seen;       // the last calls launched without a graph (exec null)
@@ -355,10 +363,10 @@ hipError_t enqueue(su2_plan_s* pl, int which, int dir, const void* in, void* out
   switch (which) {
     case 0:
     case 3: {
-      // the groups with launches of their own run on a second branch beside
-      // the register-resident list (fork/join through events, also inside a
-      // stream capture)
-      const bool both = ms->n_ringf > 0 && !ms->dedicated.empty();
+      // the mixed-radix list and the groups with launches of their own run on a
+      // second branch beside the register-resident list (fork/join through
+      // events, also inside a stream capture)
+      const bool both = ms->n_ringf > 0 && (!ms->dedicated.empty() || ms->n_radix > 0);
       hipStream_t sg = both ? ms->side : s;
       hipError_t e;
       if (both) {
@@ -368,15 +376,27 @@ hipError_t enqueue(su2_plan_s* pl, int which, int dir, const void* in, void* out
       int d = which == 0 ? 0 : dir;
       const cpx<T>* xin = (const cpx<T>*)in;
       cpx<T>* xout = (cpx<T>*)out;
-      void* args[] = {nullptr, nullptr, (void*)&g, (void*)&xin, (void*)&xout, (void*)&d};
-      for (int gi : ms->dedicated)
-        if ((e = launch_group_rings<T>(ms->groups[gi], which == 0, d, in, out, sg)) != hipSuccess) return e;
-      if (ms->n_ringf > 0) {
-        args[0] = (void*)&ms->d_ringf;
-        args[1] = (void*)&ms->n_ringf;
-        if ((e = hipLaunchKernel(ringf_kernel_ptr<T>(which == 0, pl->real), grid_of(ms->n_ringf), dim3(FAST_NT), args,
-                                 ms->smem_ringf, s)) != hipSuccess)
-          return e;
+      // The branch enqueued second starts 8 us later in a replayed graph.  The
+      // forward, whose rings come first, takes the longer branch first (B = 16,
+      // 24, 32, 48, 64 in FP64: 180 -> 170 us; twice these 204 -> 190); the
+      // inverse, whose rings follow the contractions' join, gains from the side
+      // branch first (twice these in FP32: 108 -> 96 us).
+      const bool list_first = which == 0 && ms->ringf_longer;
+      for (int turn = 0; turn < 2; turn++) {
+        if (list_first == (turn == 0)) {
+          if (ms->n_ringf == 0) continue;
+          void* args[] = {(void*)&ms->d_ringf, (void*)&ms->n_ringf, (void*)&g, (void*)&xin, (void*)&xout, (void*)&d};
+          if ((e = hipLaunchKernel(ringf_kernel_ptr<T>(which == 0, pl->real), grid_of(ms->n_ringf), dim3(FAST_NT), args,
+                                   ms->smem_ringf, s)) != hipSuccess)
+            return e;
+        } else {
+          for (int gi : ms->dedicated)
+            if ((e = launch_group_rings<T>(ms->groups[gi], which == 0, d, in, out, sg)) != hipSuccess) return e;
+          if (ms->n_radix > 0 &&
+              (e = launch_radix_list<T>(which == 0, d, ms->d_radix, ms->n_radix, ms->smem_radix,
+                                        (const RadixListGroup<T>*)ms->d_radix_groups, xin, xout, sg)) != hipSuccess)
+            return e;
+        }
       }
       if (both) {
         if ((e = hipEventRecord(ms->join, ms->side)) != hipSuccess) return e;
@@ -468,6 +488,52 @@ hipError_t set_worklist_smem(su2_plan_s* pl) {
   return hipSuccess;
 }
 
+// The mixed-radix groups that share one ring launch: those whose own launches
+// would be less than two workgroups per CU, if there are two or more (they are
+// taken out of ms->dedicated).  One launch per group -> one for all, us, forward /
+// inverse: one signal each of B = 1, 2, 3, 4, 6, 9, 12, 18 in FP32 40.6 -> 18.4 /
+// 63.7 -> 36.0; of B = 9, 12, 18, 24, 27, 36, 48, 54 130 -> 105 / 119 -> 93; four of
+// each 153 -> 129 / 144 -> 119.  A group with more workgroups fills the chip with
+// its own, faster shape.  Set up once: the ring tasks do not depend on the tile
+// shapes.
+template <class T>
+hipError_t build_radix_list(MixedState* ms) {
+  std::vector<std::pair<int, int>> small;  // (blocks, group)
+  for (int gi : ms->dedicated) {
+    const su2_plan_s* gp = ms->groups[gi];
+    const int nb = gp->large ? 0 : radix_list_blocks<T>(gp->N, (long long)gp->batch * gp->N);
+    if (nb > 0 && nb < 2 * ms->num_cu) small.push_back({nb, gi});
+  }
+  if (small.size() < 2) return hipSuccess;
+  // the longest rings first
+  std::stable_sort(small.begin(), small.end(), [&](const std::pair<int, int>& x, const std::pair<int, int>& y) {
+    return ms->groups[x.second]->N > ms->groups[y.second]->N;
+  });
+  std::vector<RadixListGroup<T>> hg(ms->groups.size());
+  memset(hg.data(), 0, sizeof(RadixListGroup<T>) * hg.size());
+  std::vector<int2> items;
+  for (auto& x : small) {
+    su2_plan_s* gp = ms->groups[x.second];
+    for (int dir = 0; dir < 3; dir++) hg[x.second].p[dir] = radix_params<T>(gp, dir == 2);
+    hg[x.second].S = (cpx<T>*)gp->d_S;
+    ms->smem_radix = std::max(ms->smem_radix, radix_list_smem<T>(gp->N));
+    for (int i = 0; i < x.first; i++) items.push_back(make_int2(x.second, i));
+    ms->dedicated.erase(std::find(ms->dedicated.begin(), ms->dedicated.end(), x.second));
+  }
+  hipError_t e;
+  if (!ms->d_radix) {
+    if ((e = mixed_alloc(ms, &ms->d_radix_groups, sizeof(RadixListGroup<T>) * hg.size())) != hipSuccess) return e;
+    if ((e = mixed_alloc(ms, (void**)&ms->d_radix, sizeof(int2) * items.size())) != hipSuccess) return e;
+    if ((e = hipMemcpy(ms->d_radix_groups, hg.data(), sizeof(RadixListGroup<T>) * hg.size(),
+                       hipMemcpyHostToDevice)) != hipSuccess)
+      return e;
+    if ((e = hipMemcpy(ms->d_radix, items.data(), sizeof(int2) * items.size(), hipMemcpyHostToDevice)) != hipSuccess)
+      return e;
+  }
+  ms->n_radix = (int)items.size();
+  return hipSuccess;
+}
+
 // build the per-group device descriptors, work lists and LDS sizes from the
 // plan's tile shapes (ms->kc, ms->narrow_f, ms->narrow_i); only_group >= 0
 // keeps only that group's contraction tasks (the autotuner times one group's
@@ -491,6 +557,7 @@ su2_status_t build_worklists(su2_plan_s* pl, int only_group = -1) {
   std::vector<GroupDev<T>> hg(ng);
   std::vector<std::pair<double, WorkItem>> ringf, betaf, betai;
   int cap_f = 0, cap_i = 0;
+  double ring_work[2] = {0, 0};  // others, register-resident
   ms->rtmax = 1;
   ms->dedicated.clear();
   for (int gi = 0; gi < ng; gi++) {
@@ -515,6 +582,7 @@ su2_status_t build_worklists(su2_plan_s* pl, int only_group = -1) {
     const int N = gp->N;
     // ring LDS
     const double ring_cost = (double)N * N * (N > 1 ? std::log2((double)N) : 1.0);
+    ring_work[gp->fast ? 1 : 0] += ring_cost * N * gp->batch;
     if (!gp->fast) {
       ms->dedicated.push_back(gi);  // launched whole by launch_group_rings
     } else {
@@ -537,6 +605,9 @@ su2_status_t build_worklists(su2_plan_s* pl, int only_group = -1) {
         betai.push_back({tile_cost * std::min(bti, gp->batch - b * bti), WorkItem{gi, t, b}});
     }
   }
+  hipError_t e;
+  ms->ringf_longer = ring_work[1] >= ring_work[0];
+  if ((e = build_radix_list<T>(ms)) != hipSuccess) return hip_fail(e);
   if (bf) {
     ms->smem_betaf = XBF_SMEM;
     ms->smem_betai = XBI_SMEM;
@@ -547,7 +618,6 @@ su2_status_t build_worklists(su2_plan_s* pl, int only_group = -1) {
   auto by_cost = [](const std::pair<double, WorkItem>& x, const std::pair<double, WorkItem>& y) {
     return x.first > y.first;
   };
-  hipError_t e;
   if (first) {
     ms->max_betaf = cap_f;
     ms->max_betai = cap_i;

@@ -44,6 +44,8 @@
 // signals 291 / 293 -> 99 / 94 us; N = 72 FP32, 44 signals 140 / 142 -> 49 / 54 us;
 // N = 96 FP32, 18 signals 93 / 83 -> 47 / 59 us; N = 192 FP32, 2 signals
 // 278 / 280 -> 62 / 74 us; N = 216 FP64, 2 signals 799 / 968 -> 264 / 228 us.
+#include <algorithm>
+
 #include "su2fft_fused.h"
 
 namespace su2 {
@@ -604,37 +606,38 @@ __host__ __device__ inline unsigned radix_grid(long long rings) {
 
 // dynamic LDS of a workgroup: the column table where it fits (it does not in
 // the FP64 inverse at N = 192), the roots, the slices
-template <class T, int N, bool FWD, class C>
+template <class T, int N, bool FWD, class C, int RPW = C::RPW>
 constexpr size_t radix_lds_values() {
-  return 2 * N + (size_t)C::RPW * std::conditional<FWD, RadixForward<T, N, C>, RadixInverse<T, N, C>>::type::LDS;
+  return 2 * N + (size_t)RPW * std::conditional<FWD, RadixForward<T, N, C>, RadixInverse<T, N, C>>::type::LDS;
 }
-template <class T, int N, bool FWD, class C>
+template <class T, int N, bool FWD, class C, int RPW = C::RPW>
 constexpr bool radix_cols_in_lds() {
-  return sizeof(int4) * N + radix_lds_values<T, N, FWD, C>() * sizeof(cpx<T>) <= 160 * 1024;
+  return sizeof(int4) * N + radix_lds_values<T, N, FWD, C, RPW>() * sizeof(cpx<T>) <= 160 * 1024;
 }
 
-template <class T, int N, bool FWD, class C>
-__global__ __launch_bounds__((C::NTR * C::RPW)) void ring_radix_kernel(const cpx<T>* __restrict__ in,
-                                                                       cpx<T>* __restrict__ out, RadixRingParams<T> p) {
+// workgroup blk of a launch of one length: RPW slices, NT threads
+template <class T, int N, bool FWD, class C, int RPW = C::RPW, int NT = C::NTR * RPW>
+__device__ __forceinline__ void radix_workgroup(const cpx<T>* __restrict__ in, cpx<T>* __restrict__ out,
+                                                const RadixRingParams<T>& p, int blk, unsigned char* smem_raw) {
   typedef typename std::conditional<FWD, RadixForward<T, N, C>, RadixInverse<T, N, C>>::type X;
-  constexpr int RPW = C::RPW, NTR = C::NTR;
-  extern __shared__ __align__(16) unsigned char smem_raw[];
+  constexpr int NTR = C::NTR;
   // the column table and the roots, in LDS for the whole workgroup (a column's
   // entry read from memory would put its latency in front of the spectra's)
-  constexpr bool CL = radix_cols_in_lds<T, N, FWD, C>();
+  constexpr bool CL = radix_cols_in_lds<T, N, FWD, C, RPW>();
   int4* lcols = reinterpret_cast<int4*>(smem_raw);
   cpx<T>* tw = reinterpret_cast<cpx<T>*>(lcols + (CL ? N : 0));
   if constexpr (CL)
-    for (int u = threadIdx.x; u < N; u += NTR * RPW) lcols[u] = p.cols[u];
+    for (int u = threadIdx.x; u < N; u += NT) lcols[u] = p.cols[u];
   const int4* cols = CL ? lcols : p.cols;
-  for (int u = threadIdx.x; u < 2 * N; u += NTR * RPW) tw[u] = p.tw[u];
-  const int sub = RPW == 1 ? 0 : threadIdx.x / NTR, t = RPW == 1 ? threadIdx.x : threadIdx.x - sub * NTR;
-  cpx<T>* buf = tw + 2 * N + sub * X::LDS;
+  for (int u = threadIdx.x; u < 2 * N; u += NT) tw[u] = p.tw[u];
+  const int sub = NT == NTR ? 0 : threadIdx.x / NTR, t = NT == NTR ? threadIdx.x : threadIdx.x - sub * NTR;
+  const bool live = NT == NTR * RPW || sub < RPW;  // threads beyond the slices only take part in the barriers
+  cpx<T>* buf = tw + 2 * N + (live ? sub : 0) * X::LDS;
   int ring, s;
-  radix_slot<C::R, RPW>(blockIdx.x, sub, &ring, &s);
+  radix_slot<C::R, RPW>(blk, sub, &ring, &s);
   // forward rings node-major over the signals, inverse rings signal-major:
   // the orders of the register-resident kernels, for the same reasons
-  const bool ok = ring < p.batch * N;
+  const bool ok = live && ring < p.batch * N;
   const int rr = ok ? ring : 0;
   const int b = FWD ? rr % p.batch : rr / N, k = FWD ? rr / p.batch : rr % N;
   const size_t x0 = ring_offset(p.soff, b, N) + (size_t)k * N * N;
@@ -644,23 +647,30 @@ __global__ __launch_bounds__((C::NTR * C::RPW)) void ring_radix_kernel(const cpx
     const cpx<T>* x = p.real_io ? reinterpret_cast<const cpx<T>*>(reinterpret_cast<const T*>(in) + x0) : in + x0;
     if (ok) X::forward1(x, buf, tw, p.tw, s, p.real_io, t);
     __syncthreads();
-    X::forward2(buf, t);
+    if (live) X::forward2(buf, t);
     __syncthreads();
-    X::forward3(buf, tw, s, p.so3, t);
+    if (live) X::forward3(buf, tw, s, p.so3, t);
     __syncthreads();
-    X::forward4(buf, t);
+    if (live) X::forward4(buf, t);
     __syncthreads();
     if (ok) X::forward5(buf, out + s0, tile_step, cols, p.W[k], s, t);
   } else {
     cpx<T>* x = p.real_io ? reinterpret_cast<cpx<T>*>(reinterpret_cast<T*>(out) + x0) : out + x0;
     if (ok) X::inverse1(in + s0, tile_step, buf, tw, p.tw, cols, p.adjoint ? p.W[k] : T(1), s, t);
     __syncthreads();
-    X::inverse2(buf, tw, s, p.so3, t);
+    if (live) X::inverse2(buf, tw, s, p.so3, t);
     __syncthreads();
-    X::inverse3(buf, tw, t);
+    if (live) X::inverse3(buf, tw, t);
     __syncthreads();
     if (ok) X::inverse4(buf, x, s, p.real_io, t);
   }
+}
+
+template <class T, int N, bool FWD, class C>
+__global__ __launch_bounds__((C::NTR * C::RPW)) void ring_radix_kernel(const cpx<T>* __restrict__ in,
+                                                                       cpx<T>* __restrict__ out, RadixRingParams<T> p) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  radix_workgroup<T, N, FWD, C>(in, out, p, blockIdx.x, smem_raw);
 }
 
 template <class T, int N, bool FWD, class C = RadixCfg<T, N, FWD>>
@@ -690,6 +700,88 @@ static hipError_t launch_radix_any(const RadixRingParams<T>& p, const cpx<T>* in
   }
   return hipErrorInvalidValue;
 }
+
+// ---- several lengths in one launch (mixed plans) ----
+//
+// Groups of a few rings leave the chip idle one launch after another.  Here a
+// workgroup takes its group and workgroup number from a list and runs its
+// length's shape, with as many rings as fit the list's workgroup (the shape's own
+// threads per ring, so that the compiler forms the same products and sums and
+// the bits are those of the length's own launch).  Up to N = 54: longer rings
+// want more threads and LDS than the short ones beside them can share.
+template <class T>
+constexpr int radix_list_threads() { return sizeof(T) == 4 ? 256 : 384; }  // the longest shape's
+template <class T, int N, bool FWD>
+struct RadixListShape {
+  typedef RadixCfg<T, N, FWD> C;
+  static_assert(C::R == 1, "whole rings");
+  static constexpr int NT = radix_list_threads<T>(), RPW = NT / C::NTR;
+  static_assert(RPW == NT / RadixCfg<T, N, !FWD>::NTR, "one list for both directions");
+  static constexpr size_t smem = sizeof(int4) * N + radix_lds_values<T, N, FWD, C, RPW>() * sizeof(cpx<T>);
+  static_assert(smem <= 64 * 1024, "no attribute needed");
+};
+#define SU2_RADIX_LIST(X) X(2) X(4) X(6) X(8) X(12) X(18) X(24) X(36) X(48) X(54)
+
+template <class T, bool FWD>
+__global__ __launch_bounds__(radix_list_threads<T>()) void ring_radix_list_kernel(
+    const int2* __restrict__ items, const RadixListGroup<T>* __restrict__ groups, const cpx<T>* __restrict__ in,
+    cpx<T>* __restrict__ out, int dir) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  const int2 w = items[blockIdx.x];
+  const RadixRingParams<T> p = groups[w.x].p[dir];
+  const cpx<T>* src = FWD ? in : groups[w.x].S;
+  cpx<T>* dst = FWD ? groups[w.x].S : out;
+  switch (p.N) {
+#define SU2_RADIX_CASE(NN)                                                                                         \
+  case NN:                                                                                                         \
+    radix_workgroup<T, NN, FWD, RadixCfg<T, NN, FWD>, RadixListShape<T, NN, FWD>::RPW, radix_list_threads<T>()>(   \
+        src, dst, p, w.y, smem_raw);                                                                               \
+    break;
+    SU2_RADIX_LIST(SU2_RADIX_CASE)
+#undef SU2_RADIX_CASE
+  }
+}
+
+template <class T>
+int radix_list_blocks(int N, long long rings) {
+  switch (N) {
+#define SU2_RADIX_CASE(NN) \
+  case NN: return (int)radix_grid<1, RadixListShape<T, NN, true>::RPW>(rings);
+    SU2_RADIX_LIST(SU2_RADIX_CASE)
+#undef SU2_RADIX_CASE
+  }
+  return 0;
+}
+template int radix_list_blocks<float>(int, long long);
+template int radix_list_blocks<double>(int, long long);
+
+template <class T>
+size_t radix_list_smem(int N) {
+  switch (N) {
+#define SU2_RADIX_CASE(NN) \
+  case NN: return std::max(RadixListShape<T, NN, true>::smem, RadixListShape<T, NN, false>::smem);
+    SU2_RADIX_LIST(SU2_RADIX_CASE)
+#undef SU2_RADIX_CASE
+  }
+  return 0;
+}
+template size_t radix_list_smem<float>(int);
+template size_t radix_list_smem<double>(int);
+
+template <class T>
+hipError_t launch_radix_list(bool forward, int dir, const int2* items, int n, size_t smem,
+                             const RadixListGroup<T>* groups, const cpx<T>* in, cpx<T>* out, hipStream_t s) {
+  const dim3 grid(n), block(radix_list_threads<T>());
+  if (forward)
+    hipLaunchKernelGGL((ring_radix_list_kernel<T, true>), grid, block, smem, s, items, groups, in, out, dir);
+  else
+    hipLaunchKernelGGL((ring_radix_list_kernel<T, false>), grid, block, smem, s, items, groups, in, out, dir);
+  return hipGetLastError();
+}
+template hipError_t launch_radix_list<float>(bool, int, const int2*, int, size_t, const RadixListGroup<float>*,
+                                             const cpx<float>*, cpx<float>*, hipStream_t);
+template hipError_t launch_radix_list<double>(bool, int, const int2*, int, size_t, const RadixListGroup<double>*,
+                                              const cpx<double>*, cpx<double>*, hipStream_t);
 
 // ---- whole signals: rings and contraction in one kernel (N <= 12) ----
 //
