@@ -210,8 +210,10 @@ su2_status_t su2_forward_noalloc(su2_plan_t plan, const void* d_samples, void* d
  *   SU2_STAGE_BETA_ADJOINT, SU2_STAGE_RING_ADJOINT: the same for su2_adjoint.
  * su2_forward is exactly RING_FORWARD then BETA_FORWARD on the same stream;
  * su2_inverse is BETA_INVERSE then RING_INVERSE; su2_adjoint is BETA_ADJOINT
- * then RING_ADJOINT (plans up to B = 8 do both in one kernel, with the same
- * results and workspace bit for bit).  Single-B plans only. */
+ * then RING_ADJOINT.  Plans up to B = 8 do both in one kernel, with the same
+ * results and workspace bit for bit, at the batches where that is faster; not
+ * plans with on-the-fly tables, in SU2_C64_BF16X3, or of real signals at B = 8.
+ * Single-B plans only. */
 typedef enum {
   SU2_STAGE_RING_FORWARD = 0,
   SU2_STAGE_BETA_FORWARD = 1,

@@ -9,6 +9,7 @@
 #include <type_traits>
 #include <vector>
 
+#include "su2fft_mfma.h"
 #include "su2fft_plan.h"
 
 using namespace su2;
@@ -698,8 +699,38 @@ su2_status_t run_pair(su2_plan_s* pl, su2_stage_t first, su2_stage_t second, con
 // 15.0 -> 10.4 / 15.8 -> 11.3; B = 6, 1 signal 7.8 -> 5.5 / 7.8 -> 6.1; FP32 B = 4,
 // 1 signal 6.5 -> 3.5 / 6.7 -> 4.2.  At B = 9 one workgroup's rings and products
 // take longer than a second launch (FP64, 1 signal 7.6 -> 14.4 / 10.8 -> 13.2).
-bool fused_call(const su2_plan_s* pl) {
-  return pl->B <= 8 && !pl->otf && pl->dtype != SU2_C64_BF16X3 && !(pl->real && !pl->real_io);
+//
+// Up to N = 8 that holds at any batch (FP64 B = 4, 16384 signals 103 -> 63 /
+// 110 -> 68).  At N = 12 and 16 a signal takes a CU's LDS or threads to itself,
+// and from some signals per CU on the vector FMAs of its products cost more than
+// the second launch and the spectra's way through the caches:
+// * FP64 forward at N = 12, 5 signals per CU: 1280 signals 25.2 -> 24.3, 1536
+//   26.5 -> 28.3, 16384 230 -> 276; at N = 16 and in FP32 it stays ahead or within
+//   2 % (N = 16, 16384 signals FP64 469 -> 411, FP32 275 -> 250; N = 12 FP32 159 -> 146).
+// * SU(2) inverse, FP64: N = 16, 5 per CU (1280 signals 45.1 -> 45.0, 2048 61.9 ->
+//   68.4, 8192 239 -> 301), N = 12, 24 per CU (6144 signals 77.5 -> 77.9, 16384
+//   183 -> 199); FP32: 12 per CU (N = 12, 3072 signals 34.8 -> 33.3, 4096 41.4 ->
+//   43.3, 16384 132 -> 159; N = 16, 4096 signals 54.0 -> 55.6, 12288 147 -> 153),
+//   but again, FP64 at N = 16 apart, where the spectra outgrow the 256 MB of
+//   last-level cache (FP32 N = 16, 16384 signals 289 -> 240, 32768 593 -> 480;
+//   FP64 N = 12, 32768 signals 579 -> 467).
+// * SO(3) inverse, half the pairs: ahead at N = 16 (FP64, 16384 signals 477 -> 351;
+//   FP32 174 -> 164), in FP64 at N = 12 too (176 -> 175); FP32 at N = 12, 16 per CU
+//   (4096 signals 41.3 -> 39.0, 6144 53.9 -> 55.8).
+bool fused_call(const su2_plan_s* pl, bool forward) {
+  if (pl->B > 8 || pl->otf || pl->dtype == SU2_C64_BF16X3 || (pl->real && !pl->real_io)) return false;
+  if (pl->N < 12) return true;
+  const bool dbl = pl->dtype == SU2_C128, n12 = pl->N == 12;
+  int per_cu = 0;  // signals per CU; 0: any
+  if (forward)
+    per_cu = dbl && n12 ? 5 : 0;
+  else if (pl->so3)
+    per_cu = !dbl && n12 ? 16 : 0;
+  else
+    per_cu = dbl ? (n12 ? 24 : 5) : 12;
+  if (per_cu == 0 || pl->batch <= per_cu * device_cus()) return true;
+  const size_t spectra = (dbl ? 16 : 8) * (size_t)pl->P_pad * pl->N * pl->batch;
+  return !forward && !(dbl && !n12) && spectra >= ((size_t)256 << 20);
 }
 template <class T>
 su2_status_t run_fused(su2_plan_s* pl, bool forward, int adjoint, const void* in, void* out, hipStream_t s) {
@@ -714,7 +745,7 @@ su2_status_t run_fused(su2_plan_s* pl, bool forward, int adjoint, const void* in
 
 // a whole call of a single-B plan
 su2_status_t run_call(su2_plan_s* pl, bool forward, int adjoint, const void* in, void* out, hipStream_t s) {
-  if (fused_call(pl))
+  if (fused_call(pl, forward))
     return pl->dtype == SU2_C128 ? run_fused<double>(pl, forward, adjoint, in, out, s)
                                  : run_fused<float>(pl, forward, adjoint, in, out, s);
   if (forward) return run_pair(pl, SU2_STAGE_RING_FORWARD, SU2_STAGE_BETA_FORWARD, in, out, s);
