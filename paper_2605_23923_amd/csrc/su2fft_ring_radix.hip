@@ -11,8 +11,10 @@
 // and the inverse is the conjugate transpose network without W_k (or with it,
 // the adjoint).
 //
-// A ring is cut in R slices, one workgroup each, so that a slice fits LDS with
-// two or more workgroups per CU: the forward by gamma frequency (slice s holds
+// A ring is cut in R slices, one workgroup each, so that a slice fits LDS: two or
+// more per CU at most lengths, one (95-160 KB) at N = 192 and 216, at N = 144 in
+// FP64, in the FP32 inverse and the FP64 forward at N = 108 and in the FP64 forward at
+// N = 162.  The forward is cut by gamma frequency (slice s holds
 // q = R q' + s; the first radix-R step of the gamma transform is taken while
 // the samples are read), the inverse by output row (slice s holds
 // j = R j' + s; the bins fold into an (N / R)-point alpha transform while the
@@ -51,6 +53,26 @@
 namespace su2 {
 
 #define SU2_HD __host__ __device__ __forceinline__
+
+// Every multiply-add below is written out, and the compiler forms none of its
+// own: which ones it picks depends on the code around them, and a length's rings
+// have the same bits in its own launch, in a list beside other lengths and in the
+// one-kernel calls.
+#pragma clang fp contract(off)
+template <class T>
+SU2_HD T fma_of(T a, T b, T c) { return __builtin_elementwise_fma(a, b, c); }
+template <class T>
+SU2_HD cpx<T> mul(cpx<T> a, cpx<T> w) {
+  return {fma_of(a.re, w.re, -(a.im * w.im)), fma_of(a.re, w.im, a.im * w.re)};
+}
+template <class T>
+SU2_HD cpx<T> mul_conj(cpx<T> a, cpx<T> w) {  // a conj(w)
+  return {fma_of(a.re, w.re, a.im * w.im), fma_of(a.im, w.re, -(a.re * w.im))};
+}
+template <class T>
+SU2_HD cpx<T> mul_add(cpx<T> a, cpx<T> w, cpx<T> c) {  // a w + c
+  return {fma_of(a.re, w.re, fma_of(-a.im, w.im, c.re)), fma_of(a.re, w.im, fma_of(a.im, w.re, c.im))};
+}
 
 // e^{2 pi i k / 288}, the first octant: every root that the DFTs and the
 // half-bin shifts below need (lengths dividing 288) follows by symmetry
@@ -105,15 +127,25 @@ SU2_HD cpx<T> rot(cpx<T> a) {
   else if constexpr (u == 216) return {a.im, -a.re};
   else {
     constexpr T wr = T(root_re(SIGN * K, LEN)), wi = T(root_im(SIGN * K, LEN));
-    return {a.re * wr - a.im * wi, a.re * wi + a.im * wr};
+    return mul(a, cpx<T>{wr, wi});
   }
 }
 
+constexpr int inverse_mod(int a, int m) {
+  for (int i = 1; i < m; i++)
+    if (a * i % m == 1) return i;
+  return 0;  // not coprime
+}
 // In-register DFT of length R: a[q] <- sum_n a[n] e^{SIGN 2 pi i q n / R}, by
-// R = P Q with P = 4, 3 or 2 outside and Q inside.
+// R = P Q.  Coprime P and Q (6 = 2 x 3, 12 = 4 x 3, 18 = 2 x 9) need no twiddles
+// between them under the prime-factor index maps n = Q n1 + P n2 and
+// q = EP k1 + EQ k2 (mod R; I. J. Good, 1958), which also saves their rounding:
+// the rings' errors are 1-8 % smaller than with twiddles.
 template <class T, int R, int SIGN>
 struct Dft {
-  static constexpr int P = R % 4 == 0 ? (R == 8 ? 2 : (R == 12 ? 3 : 4)) : (R % 3 == 0 ? 3 : 2), Q = R / P;
+  static constexpr int P = R == 9 ? 3 : (R == 12 || R == 16 ? 4 : 2), Q = R / P;
+  static constexpr int EP = Q * inverse_mod(Q % P, P), EQ = P * inverse_mod(P % Q, Q);
+  static constexpr bool PRIME_FACTOR = EP != 0 && EQ != 0;
   template <int N1, int K2>
   SU2_HD static void twiddle(cpx<T> (&y)[P][Q]) {
     if constexpr (N1 < P) {
@@ -127,10 +159,10 @@ struct Dft {
 #pragma unroll
     for (int n1 = 0; n1 < P; n1++) {
 #pragma unroll
-      for (int n2 = 0; n2 < Q; n2++) y[n1][n2] = a[P * n2 + n1];
+      for (int n2 = 0; n2 < Q; n2++) y[n1][n2] = a[PRIME_FACTOR ? (Q * n1 + P * n2) % R : P * n2 + n1];
       Dft<T, Q, SIGN>::run(y[n1]);
     }
-    twiddle<1, 1>(y);
+    if constexpr (!PRIME_FACTOR) twiddle<1, 1>(y);
 #pragma unroll
     for (int k2 = 0; k2 < Q; k2++) {
       cpx<T> z[P];
@@ -138,7 +170,7 @@ struct Dft {
       for (int n1 = 0; n1 < P; n1++) z[n1] = y[n1][k2];
       Dft<T, P, SIGN>::run(z);
 #pragma unroll
-      for (int k1 = 0; k1 < P; k1++) a[k2 + Q * k1] = z[k1];
+      for (int k1 = 0; k1 < P; k1++) a[PRIME_FACTOR ? (EP * k1 + EQ * k2) % R : k2 + Q * k1] = z[k1];
     }
   }
 };
@@ -159,11 +191,10 @@ struct Dft<T, 3, SIGN> {
   SU2_HD static void run(cpx<T>* a) {
     constexpr T h = T(root_im(1, 3));
     const cpx<T> t1 = cadd(a[1], a[2]), t2 = csub(a[1], a[2]);
-    const cpx<T> m1 = {a[0].re - T(0.5) * t1.re, a[0].im - T(0.5) * t1.im};
-    const cpx<T> m2 = {-T(SIGN) * h * t2.im, T(SIGN) * h * t2.re};
+    const cpx<T> m = {fma_of(T(-0.5), t1.re, a[0].re), fma_of(T(-0.5), t1.im, a[0].im)};
     a[0] = cadd(a[0], t1);
-    a[1] = cadd(m1, m2);
-    a[2] = csub(m1, m2);
+    a[1] = {fma_of(-T(SIGN) * h, t2.im, m.re), fma_of(T(SIGN) * h, t2.re, m.im)};
+    a[2] = {fma_of(T(SIGN) * h, t2.im, m.re), fma_of(-T(SIGN) * h, t2.re, m.im)};
   }
 };
 template <class T, int SIGN>
@@ -178,13 +209,35 @@ struct Dft<T, 4, SIGN> {
   }
 };
 
+// 8 = 2 x 4, the products with the eighth roots inside the last additions
+template <class T, int SIGN>
+struct Dft<T, 8, SIGN> {
+  SU2_HD static void run(cpx<T>* a) {
+    constexpr T h = T(root_re(1, 8)), g = T(SIGN) * h;
+    cpx<T> e[4] = {a[0], a[2], a[4], a[6]}, o[4] = {a[1], a[3], a[5], a[7]};
+    Dft<T, 4, SIGN>::run(e);
+    Dft<T, 4, SIGN>::run(o);
+    o[2] = rot<T, 1, 4, SIGN>(o[2]);
+    a[0] = cadd(e[0], o[0]);
+    a[4] = csub(e[0], o[0]);
+    a[2] = cadd(e[2], o[2]);
+    a[6] = csub(e[2], o[2]);
+    const T p = o[1].re - T(SIGN) * o[1].im, q = o[1].im + T(SIGN) * o[1].re;
+    const T r = -o[3].re - T(SIGN) * o[3].im, t = -o[3].im + T(SIGN) * o[3].re;
+    a[1] = {fma_of(h, p, e[1].re), fma_of(h, q, e[1].im)};
+    a[5] = {fma_of(-h, p, e[1].re), fma_of(-h, q, e[1].im)};
+    a[3] = {fma_of(h, r, e[3].re), fma_of(h, t, e[3].im)};
+    a[7] = {fma_of(-h, r, e[3].re), fma_of(-h, t, e[3].im)};
+  }
+};
+
 // a[j] *= e^{SIGN pi i j / LEN} where `odd`, j = 1 .. LEN - 1
 template <class T, int LEN, int SIGN, int J = 1>
 SU2_HD void half_bins(cpx<T>* a, bool odd) {
   if constexpr (J < LEN) {
     constexpr T c = T(root_re(SIGN * J, 2 * LEN)), s = T(root_im(SIGN * J, 2 * LEN));
     const T wr = odd ? c : T(1), wi = odd ? s : T(0);
-    a[J] = {a[J].re * wr - a[J].im * wi, a[J].re * wi + a[J].im * wr};
+    a[J] = mul(a[J], cpx<T>{wr, wi});
     half_bins<T, LEN, SIGN, J + 1>(a, odd);
   }
 }
@@ -195,7 +248,11 @@ SU2_HD void half_bins(cpx<T>* a, bool odd) {
 // fastest of up to 24 per (N, type, direction) at 1 signal and at about 400 MB
 // of samples (geometric mean): few slices (each reads the whole ring), enough
 // threads that a phase is one to three instances per thread, and AA a
-// multiple of 4 where the pruning of the last alpha DFT pays.
+// multiple of 4 where the pruning of the last alpha DFT pays.  At N = 12, 24 and
+// 36 they are the fastest of those whose rounding error is no larger than that of
+// one radix per pass (N = 36 FP32, forward / inverse at 256 signals 34.7 / 33.7 ->
+// 31.1 / 31.3 us with errors 5-8 % smaller; N = 12 costs up to 5 % of a call for
+// 1-10 %).
 template <int R_, int NTR_, int RPW_, int GA_, int GB_, int AA_, int AB_>
 struct RadixFwd {
   static constexpr int R = R_, NTR = NTR_, RPW = RPW_, GA = GA_, GB = GB_, AA = AA_, AB = AB_;
@@ -213,15 +270,16 @@ template <class T> struct RadixCfg<T, 4, false> : RadixInv<1, 16, 16, 4, 1, 4, 1
 template <class T> struct RadixCfg<T, 6, true> : RadixFwd<1, 32, 8, 3, 2, 3, 2> {};
 template <class T> struct RadixCfg<T, 6, false> : RadixInv<1, 32, 8, 3, 2, 2, 3> {};
 template <class T> struct RadixCfg<T, 8, true> : RadixFwd<1, 32, 8, 4, 2, 4, 2> {};
-template <class T> struct RadixCfg<T, 8, false> : RadixInv<1, 32, 8, 4, 2, 2, 4> {};
-template <class T> struct RadixCfg<T, 12, true> : RadixFwd<1, 64, 4, 4, 3, 4, 3> {};
-template <class T> struct RadixCfg<T, 12, false> : RadixInv<1, 64, 4, 4, 3, 3, 4> {};
+template <> struct RadixCfg<float, 8, false> : RadixInv<1, 32, 8, 4, 2, 8, 1> {};
+template <> struct RadixCfg<double, 8, false> : RadixInv<1, 32, 8, 4, 2, 2, 4> {};
+template <class T> struct RadixCfg<T, 12, true> : RadixFwd<1, 64, 4, 3, 4, 3, 4> {};
+template <class T> struct RadixCfg<T, 12, false> : RadixInv<1, 64, 4, 4, 3, 4, 3> {};
 template <class T> struct RadixCfg<T, 18, true> : RadixFwd<1, 64, 4, 6, 3, 6, 3> {};
 template <class T> struct RadixCfg<T, 18, false> : RadixInv<1, 64, 4, 6, 3, 3, 6> {};
-template <> struct RadixCfg<float, 24, true> : RadixFwd<1, 96, 1, 8, 3, 8, 3> {};
+template <> struct RadixCfg<float, 24, true> : RadixFwd<1, 96, 1, 4, 6, 12, 2> {};
 template <> struct RadixCfg<float, 24, false> : RadixInv<1, 96, 1, 4, 6, 3, 8> {};
-template <> struct RadixCfg<float, 36, true> : RadixFwd<1, 192, 1, 9, 4, 4, 9> {};
-template <> struct RadixCfg<float, 36, false> : RadixInv<1, 192, 1, 9, 4, 9, 4> {};
+template <> struct RadixCfg<float, 36, true> : RadixFwd<1, 192, 1, 3, 12, 12, 3> {};
+template <> struct RadixCfg<float, 36, false> : RadixInv<1, 192, 1, 9, 4, 3, 12> {};
 template <> struct RadixCfg<float, 48, true> : RadixFwd<1, 192, 1, 8, 6, 12, 4> {};
 template <> struct RadixCfg<float, 48, false> : RadixInv<1, 192, 1, 12, 4, 3, 16> {};
 template <> struct RadixCfg<float, 54, true> : RadixFwd<1, 256, 1, 9, 6, 9, 6> {};
@@ -240,10 +298,10 @@ template <> struct RadixCfg<float, 192, true> : RadixFwd<2, 768, 1, 16, 6, 16, 1
 template <> struct RadixCfg<float, 192, false> : RadixInv<3, 1024, 1, 16, 4, 12, 16> {};
 template <> struct RadixCfg<float, 216, true> : RadixFwd<3, 1024, 1, 18, 4, 12, 18> {};
 template <> struct RadixCfg<float, 216, false> : RadixInv<3, 1024, 1, 18, 4, 18, 12> {};
-template <> struct RadixCfg<double, 24, true> : RadixFwd<1, 96, 1, 4, 6, 8, 3> {};
-template <> struct RadixCfg<double, 24, false> : RadixInv<1, 96, 1, 8, 3, 3, 8> {};
-template <> struct RadixCfg<double, 36, true> : RadixFwd<1, 192, 1, 9, 4, 4, 9> {};
-template <> struct RadixCfg<double, 36, false> : RadixInv<1, 192, 1, 9, 4, 9, 4> {};
+template <> struct RadixCfg<double, 24, true> : RadixFwd<1, 96, 1, 4, 6, 12, 2> {};
+template <> struct RadixCfg<double, 24, false> : RadixInv<1, 96, 1, 4, 6, 3, 8> {};
+template <> struct RadixCfg<double, 36, true> : RadixFwd<1, 192, 1, 3, 12, 12, 3> {};
+template <> struct RadixCfg<double, 36, false> : RadixInv<1, 192, 1, 9, 4, 3, 12> {};
 template <> struct RadixCfg<double, 48, true> : RadixFwd<1, 384, 1, 8, 6, 8, 6> {};
 template <> struct RadixCfg<double, 48, false> : RadixInv<1, 384, 1, 8, 6, 6, 8> {};
 template <> struct RadixCfg<double, 54, true> : RadixFwd<1, 256, 1, 9, 6, 6, 9> {};
@@ -291,7 +349,7 @@ template <class T>
 SU2_HD cpx<T> ipow_times(cpx<T> v, int e, T s) {
   const T ss = (e & 2) ? -s : s;
   const T c = (e & 1) ? T(0) : ss, d = (e & 1) ? ss : T(0);
-  return {v.re * c - v.im * d, v.re * d + v.im * c};
+  return mul(v, cpx<T>{c, d});
 }
 
 // One slice s of one ring; t is the thread's index among the slice's NTR.
@@ -337,10 +395,10 @@ struct RadixForward : RadixThreads<C_> {
     for (int l2 = 0; l2 < GB; l2++) {
       a[l2] = sample<REAL>(x, j * N + l1 + GA * l2);
       if constexpr (R > 1) {
-        if (l2 > 0) a[l2] = cmul(a[l2], twg[2 * ((s * GA * l2) % N)]);
+        if (l2 > 0) a[l2] = mul(a[l2], twg[2 * ((s * GA * l2) % N)]);
 #pragma unroll
         for (int i = 1; i < R; i++)
-          a[l2] = cadd(a[l2], cmul(sample<REAL>(x, j * N + l1 + GA * l2 + i * M), twg[2 * ((s * (GA * l2 + i * M)) % N)]));
+          a[l2] = mul_add(sample<REAL>(x, j * N + l1 + GA * l2 + i * M), twg[2 * ((s * (GA * l2 + i * M)) % N)], a[l2]);
       }
     }
   }
@@ -365,7 +423,7 @@ struct RadixForward : RadixThreads<C_> {
 #pragma unroll
         for (int q2 = 0; q2 < GB; q2++) {
           // w_M^{l1 q2} w_N^{l1 s}
-          if (q2 > 0 || R > 1) a[u][q2] = cmul(a[u][q2], tw[2 * l1 * (R * q2 + s)]);
+          if (q2 > 0 || R > 1) a[u][q2] = mul(a[u][q2], tw[2 * l1 * (R * q2 + s)]);
           buf[j * FP + l1 + GA * q2] = a[u][q2];
         }
       }
@@ -411,7 +469,7 @@ struct RadixForward : RadixThreads<C_> {
       half_bins<T, AB, 1>(a, odd != 0);
       Dft<T, AB, 1>::run(a);
 #pragma unroll
-      for (int p2 = 0; p2 < AB; p2++) col[AA * p2 * FP] = cmul(a[p2], tw[(2 * p2 + odd) * j1]);
+      for (int p2 = 0; p2 < AB; p2++) col[AA * p2 * FP] = mul(a[p2], tw[(2 * p2 + odd) * j1]);
     }
   }
 
@@ -461,7 +519,7 @@ struct RadixInverse : RadixThreads<C_> {
   static constexpr int N = N_, R = C::R, M = N / R, NTR = C::NTR, B = N / 2;
   static constexpr int A1 = C::A1, A2 = C::A2, G1 = C::G1, G2 = C::G2;
   static_assert(A1 * A2 == M && G1 * G2 == N && R * M == N, "shape");
-  static constexpr int G1P = G2 == 1 ? G1 : (G1 | 1);  // column group pitch
+  static constexpr int G1P = G2 == 1 || N <= 24 ? G1 : (G1 | 1);  // column group pitch (short rows need no pad)
   static constexpr int IP = (G2 * G1P) | 1;            // row pitch
   static constexpr int LDS = M * IP;
   // folded bins p = p' + r M: false where none is retained for any p'
@@ -496,7 +554,7 @@ struct RadixInverse : RadixThreads<C_> {
               h = ipow_times(S[(size_t)(pair / PT) * tile_step + pair % PT], -(col.e0 + 3 * ps) & 3, scale);
             }
             // w^{-s (A1 b + r M)}; the rest, w^{-s a}, rides on the twiddle
-            if (R > 1 && (b > 0 || r > 0)) h = cmulc(h, twg[2 * ((s * (A1 * b + r * M)) % N)]);
+            if (R > 1 && (b > 0 || r > 0)) h = mul_conj(h, twg[2 * ((s * (A1 * b + r * M)) % N)]);
             v[u][b] = cadd(v[u][b], h);
           }
         }
@@ -509,7 +567,7 @@ struct RadixInverse : RadixThreads<C_> {
         Dft<T, A2, -1>::run(v[u]);
 #pragma unroll
         for (int k2 = 0; k2 < A2; k2++) {
-          if (k2 > 0 || R > 1) v[u][k2] = cmulc(v[u][k2], tw[2 * a * (s + R * k2)]);
+          if (k2 > 0 || R > 1) v[u][k2] = mul_conj(v[u][k2], tw[2 * a * (s + R * k2)]);
           buf[(a + A1 * k2) * IP + inverse_col(q)] = v[u][k2];
         }
       }
@@ -532,7 +590,7 @@ struct RadixInverse : RadixThreads<C_> {
 #pragma unroll
       for (int k1 = 0; k1 < A1; k1++) {
         const cpx<T> w = tw[odd ? R * (k2 + A2 * k1) + s : 0];
-        col[k1 * IP] = cmulc(v[k1], w);
+        col[k1 * IP] = mul_conj(v[k1], w);
       }
     }
   }
@@ -550,7 +608,7 @@ struct RadixInverse : RadixThreads<C_> {
       for (int g2 = 0; g2 < G2; g2++) v[g2] = row[g2 * G1P];
       Dft<T, G2, -1>::run(v);
 #pragma unroll
-      for (int u2 = 0; u2 < G2; u2++) row[u2 * G1P] = u2 > 0 ? cmulc(v[u2], tw[2 * g1 * u2]) : v[u2];
+      for (int u2 = 0; u2 < G2; u2++) row[u2 * G1P] = u2 > 0 ? mul_conj(v[u2], tw[2 * g1 * u2]) : v[u2];
     }
   }
 
