@@ -281,11 +281,13 @@ bool beta_bf16_small_forward(const BetaParams<float>& p) {
 // B = 36, 44 signals 80 -> 76; B = 54, 20 signals 162 -> 156; B = 64, 4 signals
 // 59 -> 42, 8 signals 85 -> 80; B = 72, 12 signals 258 -> 238; B = 128, 8 signals
 // 915 -> 850.  Alone: SO(3) B = 64, 16 signals 29.9 -> 27.1, 24 signals 38.2 -> 42.0;
-// real B = 32, 22 signals in whole calls 32.0 -> 33.3; B = 64, 9 signals 37.8 -> 38.3; B = 128,
-// 1 signal 297 -> 122, 12 signals 418 -> 440.
+// B = 64, 9 signals 37.8 -> 38.3; B = 128, 1 signal 297 -> 122, 12 signals 418 -> 440.
+// Half-spectrum whole calls: B = 16, 55 signals 21.1 -> 18.5; B = 32, whose second group
+// of 8 signals fills the CUs twice, 8 signals 26.4 -> 20.6, 9 signals 26.7 -> 28.0.
 bool beta_bf16_small_inverse(const BetaParams<float>& p) {
   if (small_fills(p)) return p.batch <= (p.B > 64 && p.B <= 96 ? 12 : 8);
-  return p.batch * small_units(p) <= (!small_mirrored(p) ? 1000 : p.B <= 54 ? 4000 : 2200);
+  if (!small_mirrored(p)) return p.batch * small_units(p) <= (p.B <= 16 ? 1000 : 520);
+  return p.batch * small_units(p) <= (p.B <= 54 ? 4000 : 2200);
 }
 
 template <int RTMAX, int MIR>

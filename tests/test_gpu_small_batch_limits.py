@@ -16,7 +16,7 @@ pytestmark = pytest.mark.gpu
 
 CASES = [(B, "complex", dtype) for B in (18, 24, 27, 36, 48, 54, 64, 72, 108) for dtype in ("c64", "c128", "c64_bf16x3")]
 CASES += [(B, "so3", dtype) for B in (32, 72, 96) for dtype in ("c64", "c128", "c64_bf16x3")]
-CASES += [(B, "real", dtype) for B in (32, 64) for dtype in ("c64", "c128", "c64_bf16x3")]
+CASES += [(B, "real", dtype) for B in (16, 32, 64) for dtype in ("c64", "c128", "c64_bf16x3")]
 
 
 def _limits(B, kind, dtype):
@@ -32,7 +32,7 @@ def _limits(B, kind, dtype):
     fills, few = 4 * units >= 3 * cus, B <= 32
     if dtype == "c64_bf16x3":
         fwd = (12 if 64 < B <= 108 else 8) if fills else (2500 if few else 1800) // units
-        inv = (12 if 64 < B <= 96 else 8) if fills else (1000 if half else 4000 if B <= 54 else 2200) // units
+        inv = (12 if 64 < B <= 96 else 8) if fills else ((1000 if B <= 16 else 520) if half else 4000 if B <= 54 else 2200) // units
     elif dtype == "c64":
         fwd = (12 if B > 64 else 8) if fills else 1600 // units
         inv = (12 if B > 64 else 8) if fills else min(40, 3600 // units)
