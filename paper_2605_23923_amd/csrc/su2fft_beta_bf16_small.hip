@@ -302,8 +302,10 @@ static hipError_t launch_forward_bf16_mid(const BetaParams<float>& p, const unsi
 template <int RTMAX>
 static hipError_t launch_forward_bf16(const BetaParams<float>& p, const unsigned* tabf, const cpx<float>* S,
                                       cpx<float>* coeffs, hipStream_t s) {
-  return small_mirrored(p) ? launch_forward_bf16_mid<RTMAX, 2>(p, tabf, S, coeffs, s)
-                           : launch_forward_bf16_mid<RTMAX, 1>(p, tabf, S, coeffs, s);
+  if (small_mirrored(p)) return launch_forward_bf16_mid<RTMAX, 2>(p, tabf, S, coeffs, s);
+  // above B = 64 every list is point-symmetric and every pair carries spectra
+  if constexpr (RTMAX <= 2) return launch_forward_bf16_mid<RTMAX, 1>(p, tabf, S, coeffs, s);
+  return hipErrorInvalidValue;
 }
 
 template <int LQ, int MIR>
@@ -331,8 +333,7 @@ hipError_t launch_beta_inverse_bf16_small(const BetaParams<float>& p, const unsi
   if (beta_bf16_lq(p.B) == 1)
     return small_mirrored(p) ? launch_inverse_bf16<1, 2>(p, tabi, coeffs, S, s)
                              : launch_inverse_bf16<1, 1>(p, tabi, coeffs, S, s);
-  return small_mirrored(p) ? launch_inverse_bf16<2, 2>(p, tabi, coeffs, S, s)
-                           : launch_inverse_bf16<2, 1>(p, tabi, coeffs, S, s);
+  return small_mirrored(p) ? launch_inverse_bf16<2, 2>(p, tabi, coeffs, S, s) : hipErrorInvalidValue;  // B > 64
 }
 
 }  // namespace su2

@@ -408,7 +408,9 @@ static hipError_t launch_forward_mid(const BetaParams<T>& p, const cpx<T>* S, cp
   switch (beta_rtmax(p.B)) {
     case 1: hipLaunchKernelGGL((beta_forward_mid_kernel<T, 1, MIR>), grid, block, 0, s, S, coeffs, p, pos_end); break;
     case 2: hipLaunchKernelGGL((beta_forward_mid_kernel<T, 2, MIR>), grid, block, 0, s, S, coeffs, p, pos_end); break;
-    default: hipLaunchKernelGGL((beta_forward_mid_kernel<T, 4, MIR>), grid, block, 0, s, S, coeffs, p, pos_end); break;
+    default:  // above B = 64 every list is point-symmetric and every pair carries spectra
+      if constexpr (MIR == 1) return hipErrorInvalidValue;
+      else hipLaunchKernelGGL((beta_forward_mid_kernel<T, 4, MIR>), grid, block, 0, s, S, coeffs, p, pos_end);
   }
   return hipGetLastError();
 }
@@ -422,7 +424,9 @@ static hipError_t launch_forward_small(const BetaParams<T>& p, const cpx<T>* S, 
   switch (beta_rtmax(p.B)) {
     case 1: hipLaunchKernelGGL((beta_forward_small_kernel<T, 1, MIR>), grid, block, 0, s, S, coeffs, p, pos_end); break;
     case 2: hipLaunchKernelGGL((beta_forward_small_kernel<T, 2, MIR>), grid, block, 0, s, S, coeffs, p, pos_end); break;
-    default: hipLaunchKernelGGL((beta_forward_small_kernel<T, 4, MIR>), grid, block, 0, s, S, coeffs, p, pos_end); break;
+    default:  // above B = 64 every list is point-symmetric and every pair carries spectra
+      if constexpr (MIR == 1) return hipErrorInvalidValue;
+      else hipLaunchKernelGGL((beta_forward_small_kernel<T, 4, MIR>), grid, block, 0, s, S, coeffs, p, pos_end);
   }
   return hipGetLastError();
 }
@@ -443,7 +447,8 @@ static hipError_t launch_inverse_small(const BetaParams<T>& p, const cpx<T>* coe
   switch (beta_lq(p.B)) {
     case 4: return launch_inverse_small_lq<T, 4, MIR>(p, coeffs, S, s);
     case 8: return launch_inverse_small_lq<T, 8, MIR>(p, coeffs, S, s);
-    case 16: return launch_inverse_small_lq<T, 16, MIR>(p, coeffs, S, s);
+    case 16:  // B > 64
+      if constexpr (MIR == 2) return launch_inverse_small_lq<T, 16, MIR>(p, coeffs, S, s);
   }
   return hipErrorInvalidValue;
 }

@@ -150,19 +150,15 @@ struct FastRingParams {
 // zero imaginary part (a known zero would be folded away and change which
 // products become FMAs, and with them the rounding).
 template <class T>
-__host__ __device__ __forceinline__ T opaque_zero() {
+__device__ __forceinline__ T opaque_zero() {
   T z = T(0);
-#ifdef __HIP_DEVICE_COMPILE__
   asm volatile("" : "+v"(z));
-#endif
   return z;
 }
 // a use of v that the compiler cannot drop
 template <class T>
-__host__ __device__ __forceinline__ void keep_value(T v) {
-#ifdef __HIP_DEVICE_COMPILE__
+__device__ __forceinline__ void keep_value(T v) {
   asm volatile("" ::"v"(v));
-#endif
 }
 template <class T>
 __device__ __forceinline__ cpx<T> ld_sample(const cpx<T>* base, size_t idx, int real_io) {

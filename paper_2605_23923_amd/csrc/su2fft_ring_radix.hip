@@ -52,7 +52,7 @@
 
 namespace su2 {
 
-#define SU2_HD __host__ __device__ __forceinline__
+#define SU2_DEV __device__ __forceinline__
 
 // Every multiply-add below is written out, and the compiler forms none of its
 // own: which ones it picks depends on the code around them, and a length's rings
@@ -60,17 +60,17 @@ namespace su2 {
 // one-kernel calls.
 #pragma clang fp contract(off)
 template <class T>
-SU2_HD T fma_of(T a, T b, T c) { return __builtin_elementwise_fma(a, b, c); }
+SU2_DEV T fma_of(T a, T b, T c) { return __builtin_elementwise_fma(a, b, c); }
 template <class T>
-SU2_HD cpx<T> mul(cpx<T> a, cpx<T> w) {
+SU2_DEV cpx<T> mul(cpx<T> a, cpx<T> w) {
   return {fma_of(a.re, w.re, -(a.im * w.im)), fma_of(a.re, w.im, a.im * w.re)};
 }
 template <class T>
-SU2_HD cpx<T> mul_conj(cpx<T> a, cpx<T> w) {  // a conj(w)
+SU2_DEV cpx<T> mul_conj(cpx<T> a, cpx<T> w) {  // a conj(w)
   return {fma_of(a.re, w.re, a.im * w.im), fma_of(a.im, w.re, -(a.re * w.im))};
 }
 template <class T>
-SU2_HD cpx<T> mul_add(cpx<T> a, cpx<T> w, cpx<T> c) {  // a w + c
+SU2_DEV cpx<T> mul_add(cpx<T> a, cpx<T> w, cpx<T> c) {  // a w + c
   return {fma_of(a.re, w.re, fma_of(-a.im, w.im, c.re)), fma_of(a.re, w.im, fma_of(a.im, w.re, c.im))};
 }
 
@@ -118,7 +118,7 @@ constexpr double root_im(int k, int n) {
 
 // a e^{SIGN 2 pi i K / LEN} for compile-time K, LEN
 template <class T, int K, int LEN, int SIGN>
-SU2_HD cpx<T> rot(cpx<T> a) {
+SU2_DEV cpx<T> rot(cpx<T> a) {
   static_assert(288 % LEN == 0, "root table");
   constexpr int u = root_step(SIGN * K, LEN);
   if constexpr (u == 0) return a;
@@ -147,14 +147,14 @@ struct Dft {
   static constexpr int EP = Q * inverse_mod(Q % P, P), EQ = P * inverse_mod(P % Q, Q);
   static constexpr bool PRIME_FACTOR = EP != 0 && EQ != 0;
   template <int N1, int K2>
-  SU2_HD static void twiddle(cpx<T> (&y)[P][Q]) {
+  SU2_DEV static void twiddle(cpx<T> (&y)[P][Q]) {
     if constexpr (N1 < P) {
       y[N1][K2] = rot<T, N1 * K2, R, SIGN>(y[N1][K2]);
       if constexpr (K2 + 1 < Q) twiddle<N1, K2 + 1>(y);
       else twiddle<N1 + 1, 1>(y);
     }
   }
-  SU2_HD static void run(cpx<T>* a) {
+  SU2_DEV static void run(cpx<T>* a) {
     cpx<T> y[P][Q];
 #pragma unroll
     for (int n1 = 0; n1 < P; n1++) {
@@ -176,11 +176,11 @@ struct Dft {
 };
 template <class T, int SIGN>
 struct Dft<T, 1, SIGN> {
-  SU2_HD static void run(cpx<T>*) {}
+  SU2_DEV static void run(cpx<T>*) {}
 };
 template <class T, int SIGN>
 struct Dft<T, 2, SIGN> {
-  SU2_HD static void run(cpx<T>* a) {
+  SU2_DEV static void run(cpx<T>* a) {
     const cpx<T> t = a[0];
     a[0] = cadd(t, a[1]);
     a[1] = csub(t, a[1]);
@@ -188,7 +188,7 @@ struct Dft<T, 2, SIGN> {
 };
 template <class T, int SIGN>
 struct Dft<T, 3, SIGN> {
-  SU2_HD static void run(cpx<T>* a) {
+  SU2_DEV static void run(cpx<T>* a) {
     constexpr T h = T(root_im(1, 3));
     const cpx<T> t1 = cadd(a[1], a[2]), t2 = csub(a[1], a[2]);
     const cpx<T> m = {fma_of(T(-0.5), t1.re, a[0].re), fma_of(T(-0.5), t1.im, a[0].im)};
@@ -199,7 +199,7 @@ struct Dft<T, 3, SIGN> {
 };
 template <class T, int SIGN>
 struct Dft<T, 4, SIGN> {
-  SU2_HD static void run(cpx<T>* a) {
+  SU2_DEV static void run(cpx<T>* a) {
     const cpx<T> s02 = cadd(a[0], a[2]), d02 = csub(a[0], a[2]);
     const cpx<T> s13 = cadd(a[1], a[3]), d13 = rot<T, 1, 4, SIGN>(csub(a[1], a[3]));
     a[0] = cadd(s02, s13);
@@ -212,7 +212,7 @@ struct Dft<T, 4, SIGN> {
 // 8 = 2 x 4, the products with the eighth roots inside the last additions
 template <class T, int SIGN>
 struct Dft<T, 8, SIGN> {
-  SU2_HD static void run(cpx<T>* a) {
+  SU2_DEV static void run(cpx<T>* a) {
     constexpr T h = T(root_re(1, 8)), g = T(SIGN) * h;
     cpx<T> e[4] = {a[0], a[2], a[4], a[6]}, o[4] = {a[1], a[3], a[5], a[7]};
     Dft<T, 4, SIGN>::run(e);
@@ -233,7 +233,7 @@ struct Dft<T, 8, SIGN> {
 
 // a[j] *= e^{SIGN pi i j / LEN} where `odd`, j = 1 .. LEN - 1
 template <class T, int LEN, int SIGN, int J = 1>
-SU2_HD void half_bins(cpx<T>* a, bool odd) {
+SU2_DEV void half_bins(cpx<T>* a, bool odd) {
   if constexpr (J < LEN) {
     constexpr T c = T(root_re(SIGN * J, 2 * LEN)), s = T(root_im(SIGN * J, 2 * LEN));
     const T wr = odd ? c : T(1), wi = odd ? s : T(0);
@@ -327,26 +327,26 @@ template <> struct RadixCfg<double, 216, false> : RadixInv<6, 768, 1, 12, 3, 18,
 struct RadixCol {
   int hi, zero, lo, nneg, npos, e0;
 };
-SU2_HD RadixCol radix_col(const int4& w) {
+SU2_DEV RadixCol radix_col(const int4& w) {
   return {w.x, w.y, w.z, (w.w >> 2) & 127, (w.w >> 9) & 127, w.w & 3};
 }
-SU2_HD int radix_pair(const RadixCol& c, int ps) { return ps < 0 ? c.hi + ps : (ps == 0 ? c.zero : c.lo + ps); }
+SU2_DEV int radix_pair(const RadixCol& c, int ps) { return ps < 0 ? c.hi + ps : (ps == 0 ? c.zero : c.lo + ps); }
 
 // Samples are written once: non-temporal stores keep them from evicting the
 // spectra (N = 96 FP32, 56 signals: inverse ring 257 -> 181 us).  The
 // forward's sample reads are plain: runs of GA values share cache lines with
 // their neighbours', and non-temporal reads measured 10-16 % slower.
 template <class T>
-SU2_HD void nt_store(T* a, T v) { __builtin_nontemporal_store(v, a); }
+SU2_DEV void nt_store(T* a, T v) { __builtin_nontemporal_store(v, a); }
 template <class T>
-SU2_HD void nt_store(cpx<T>* a, cpx<T> v) {
+SU2_DEV void nt_store(cpx<T>* a, cpx<T> v) {
   __builtin_nontemporal_store(v.re, &a->re);
   __builtin_nontemporal_store(v.im, &a->im);
 }
 
 // v i^e s
 template <class T>
-SU2_HD cpx<T> ipow_times(cpx<T> v, int e, T s) {
+SU2_DEV cpx<T> ipow_times(cpx<T> v, int e, T s) {
   const T ss = (e & 2) ? -s : s;
   const T c = (e & 1) ? T(0) : ss, d = (e & 1) ? ss : T(0);
   return mul(v, cpx<T>{c, d});
@@ -359,7 +359,7 @@ template <class C>
 struct RadixThreads {
   static constexpr int NTR = C::NTR;
   static constexpr int iters(int total) { return (total + NTR - 1) / NTR; }
-  SU2_HD static bool in(int idx, int total) { return total % NTR == 0 || idx < total; }
+  SU2_DEV static bool in(int idx, int total) { return total % NTR == 0 || idx < total; }
 };
 
 template <class T, int N_, class C_>
@@ -375,12 +375,12 @@ struct RadixForward : RadixThreads<C_> {
   static constexpr int LDS = N * FP;
   // rows p1 of the last alpha DFT that can hold retained bins (p < N/4 or
   // p >= 3N/4): known at compile time where 4 divides AA
-  SU2_HD static constexpr bool kept_p1(int p1) { return AA % 4 != 0 || p1 < AA / 4 || p1 >= 3 * AA / 4; }
+  SU2_DEV static constexpr bool kept_p1(int p1) { return AA % 4 != 0 || p1 < AA / 4 || p1 >= 3 * AA / 4; }
   // instances of phase 1 whose loads are issued together
   static constexpr int BATCH1 = sizeof(T) == 4 ? 2 : 1;
 
   template <bool REAL>
-  SU2_HD static cpx<T> sample(const cpx<T>* x, int idx) {
+  SU2_DEV static cpx<T> sample(const cpx<T>* x, int idx) {
     // (opaque_zero: the transforms round real samples exactly as complex
     // samples with a zero imaginary part)
     if constexpr (REAL) return {reinterpret_cast<const T*>(x)[idx], opaque_zero<T>()};
@@ -390,7 +390,7 @@ struct RadixForward : RadixThreads<C_> {
   // the samples of phase-1 instance (row j, l1), radix-R step taken:
   // y[c] w^{-s l1} for c = l1 + GA l2 with y[c] = w^{s c} sum_i x[c + i M] w^{s i M}
   template <bool REAL>
-  SU2_HD static void load1(const cpx<T>* x, const cpx<T>* twg, int s, int j, int l1, cpx<T> (&a)[GB]) {
+  SU2_DEV static void load1(const cpx<T>* x, const cpx<T>* twg, int s, int j, int l1, cpx<T> (&a)[GB]) {
 #pragma unroll
     for (int l2 = 0; l2 < GB; l2++) {
       a[l2] = sample<REAL>(x, j * N + l1 + GA * l2);
@@ -404,7 +404,7 @@ struct RadixForward : RadixThreads<C_> {
   }
 
   template <bool REAL>
-  SU2_HD static void forward1_as(const cpx<T>* x, cpx<T>* buf, const cpx<T>* tw, const cpx<T>* twg, int s, int t) {
+  SU2_DEV static void forward1_as(const cpx<T>* x, cpx<T>* buf, const cpx<T>* tw, const cpx<T>* twg, int s, int t) {
     constexpr int TOTAL = N * GA, IT = iters(TOTAL), U = IT < BATCH1 ? IT : BATCH1;
 #pragma unroll 1
     for (int i0 = 0; i0 < IT; i0 += U) {
@@ -429,13 +429,13 @@ struct RadixForward : RadixThreads<C_> {
       }
     }
   }
-  SU2_HD static void forward1(const cpx<T>* x, cpx<T>* buf, const cpx<T>* tw, const cpx<T>* twg, int s, int real_io,
+  SU2_DEV static void forward1(const cpx<T>* x, cpx<T>* buf, const cpx<T>* tw, const cpx<T>* twg, int s, int real_io,
                               int t) {
     if (real_io) forward1_as<true>(x, buf, tw, twg, s, t);
     else forward1_as<false>(x, buf, tw, twg, s, t);
   }
 
-  SU2_HD static void forward2(cpx<T>* buf, int t) {
+  SU2_DEV static void forward2(cpx<T>* buf, int t) {
     constexpr int TOTAL = N * GB;
 #pragma unroll 1
     for (int i = 0; i < iters(TOTAL); i++) {
@@ -452,9 +452,9 @@ struct RadixForward : RadixThreads<C_> {
   }
 
   // gamma frequency of forward column c
-  SU2_HD static int forward_q(int c, int s) { return R * (c / GA + GB * (c % GA)) + s; }
+  SU2_DEV static int forward_q(int c, int s) { return R * (c / GA + GB * (c % GA)) + s; }
 
-  SU2_HD static void forward3(cpx<T>* buf, const cpx<T>* tw, int s, int so3, int t) {
+  SU2_DEV static void forward3(cpx<T>* buf, const cpx<T>* tw, int s, int so3, int t) {
     constexpr int TOTAL = M * AA;
 #pragma unroll 1
     for (int i = 0; i < iters(TOTAL); i++) {
@@ -473,7 +473,7 @@ struct RadixForward : RadixThreads<C_> {
     }
   }
 
-  SU2_HD static void forward4(cpx<T>* buf, int t) {
+  SU2_DEV static void forward4(cpx<T>* buf, int t) {
     constexpr int TOTAL = M * AB;
 #pragma unroll 1
     for (int i = 0; i < iters(TOTAL); i++) {
@@ -491,7 +491,7 @@ struct RadixForward : RadixThreads<C_> {
   }
 
   // S points at (tile 0, node k, signal b); tile_step values to the next tile
-  SU2_HD static void forward5(const cpx<T>* buf, cpx<T>* S, size_t tile_step, const int4* cols, T Wk, int s, int t) {
+  SU2_DEV static void forward5(const cpx<T>* buf, cpx<T>* S, size_t tile_step, const int4* cols, T Wk, int s, int t) {
     constexpr int TOTAL = M * B;
 #pragma unroll 2
     for (int i = 0; i < iters(TOTAL); i++) {
@@ -523,12 +523,12 @@ struct RadixInverse : RadixThreads<C_> {
   static constexpr int IP = (G2 * G1P) | 1;            // row pitch
   static constexpr int LDS = M * IP;
   // folded bins p = p' + r M: false where none is retained for any p'
-  SU2_HD static constexpr bool kept_fold(int r) { return !(4 * r * M >= N && 4 * (r * M + M - 1) < 3 * N); }
+  SU2_DEV static constexpr bool kept_fold(int r) { return !(4 * r * M >= N && 4 * (r * M + M - 1) < 3 * N); }
   static constexpr int BATCH1 = sizeof(T) == 4 ? 2 : 1;
 
-  SU2_HD static int inverse_col(int q) { return (q / G1) * G1P + q % G1; }
+  SU2_DEV static int inverse_col(int q) { return (q / G1) * G1P + q % G1; }
 
-  SU2_HD static void inverse1(const cpx<T>* S, size_t tile_step, cpx<T>* buf, const cpx<T>* tw, const cpx<T>* twg,
+  SU2_DEV static void inverse1(const cpx<T>* S, size_t tile_step, cpx<T>* buf, const cpx<T>* tw, const cpx<T>* twg,
                               const int4* cols, T scale, int s, int t) {
     constexpr int TOTAL = N * A1, IT = iters(TOTAL), U = IT < BATCH1 ? IT : BATCH1;
 #pragma unroll 1
@@ -574,7 +574,7 @@ struct RadixInverse : RadixThreads<C_> {
     }
   }
 
-  SU2_HD static void inverse2(cpx<T>* buf, const cpx<T>* tw, int s, int so3, int t) {
+  SU2_DEV static void inverse2(cpx<T>* buf, const cpx<T>* tw, int s, int so3, int t) {
     constexpr int TOTAL = N * A2;
 #pragma unroll 1
     for (int i = 0; i < iters(TOTAL); i++) {
@@ -595,7 +595,7 @@ struct RadixInverse : RadixThreads<C_> {
     }
   }
 
-  SU2_HD static void inverse3(cpx<T>* buf, const cpx<T>* tw, int t) {
+  SU2_DEV static void inverse3(cpx<T>* buf, const cpx<T>* tw, int t) {
     constexpr int TOTAL = M * G1;
 #pragma unroll 1
     for (int i = 0; i < iters(TOTAL); i++) {
@@ -613,7 +613,7 @@ struct RadixInverse : RadixThreads<C_> {
   }
 
   template <bool REAL>
-  SU2_HD static void inverse4_as(const cpx<T>* buf, cpx<T>* x, int s, int t) {
+  SU2_DEV static void inverse4_as(const cpx<T>* buf, cpx<T>* x, int s, int t) {
     constexpr int TOTAL = M * G2;
 #pragma unroll 1
     for (int i = 0; i < iters(TOTAL); i++) {
@@ -637,7 +637,7 @@ struct RadixInverse : RadixThreads<C_> {
       }
     }
   }
-  SU2_HD static void inverse4(const cpx<T>* buf, cpx<T>* x, int s, int real_io, int t) {
+  SU2_DEV static void inverse4(const cpx<T>* buf, cpx<T>* x, int s, int real_io, int t) {
     if (real_io) inverse4_as<true>(buf, x, s, t);
     else inverse4_as<false>(buf, x, s, t);
   }
@@ -647,7 +647,7 @@ struct RadixInverse : RadixThreads<C_> {
 // rings per workgroup.  R > 1 (RPW = 1): ids are dealt to the XCDs round robin
 // (id % 8), so a ring's slices take consecutive slots of one XCD.
 template <int R, int RPW>
-__host__ __device__ inline void radix_slot(int blk, int sub, int* ring, int* slice) {
+__device__ __forceinline__ void radix_slot(int blk, int sub, int* ring, int* slice) {
   if (R == 1) {
     *ring = blk * RPW + sub;
     *slice = 0;
@@ -658,7 +658,7 @@ __host__ __device__ inline void radix_slot(int blk, int sub, int* ring, int* sli
   }
 }
 template <int R, int RPW>
-__host__ __device__ inline unsigned radix_grid(long long rings) {
+inline unsigned radix_grid(long long rings) {
   return R == 1 ? (unsigned)((rings + RPW - 1) / RPW) : (unsigned)((rings + NXCD - 1) / NXCD * NXCD * R);
 }
 
