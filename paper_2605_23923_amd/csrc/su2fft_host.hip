@@ -274,9 +274,9 @@ su2_status_t build_plan(su2_plan_s* pl) {
   // (the mirror (-m, -n) of position i sits at P - 1 - i).  Padded to keep
   // that symmetry tile by tile where the plan keeps a table (the on-the-fly
   // plans keep none) and the padding fits the register-resident kernels'
-  // slices or, for the mixed-radix rings, costs at most one tile in 16 (from
-  // B = 18 up: below, the table is a few KB and the added tiles cost more
-  // than its second half): the pairs with 2m < 0, padded to whole tiles; the
+  // slices or, for the mixed-radix rings, costs at most one tile in 16 (B = 12
+  // in SU(2) and from B = 18 up: where it costs more, the table is a few KB and
+  // the added tiles outweigh its second half): the pairs with 2m < 0, padded to whole tiles; the
   // 2m = 0 run with one pad right after (0, 0) and as many pads on both ends
   // as whole tiles need; the pads of the first part again; the pairs with
   // 2m > 0.  Position i then mirrors position P_pad - 1 - i, tile t mirrors

@@ -38,14 +38,16 @@
 // Row pitches are odd (and the inverse's column groups of G1 are padded to
 // odd length), so that lanes over consecutive rows meet distinct banks.
 //
-// What bounds it: HBM in principle (N^2 + P values per ring: at N = 48 and 36
-// both directions run at 1.0-1.3 times the time a copy takes for those bytes,
-// at N = 96 1.3-1.5), and above that the slices' repeated reads through L2
-// (N = 192: 2.0-2.3 times).  Ring stage alone, forward / inverse, against
-// one-radix-per-pass kernels with run-time sizes before: N = 54 FP64, 106
-// signals 291 / 293 -> 99 / 94 us; N = 72 FP32, 44 signals 140 / 142 -> 49 / 54 us;
-// N = 96 FP32, 18 signals 93 / 83 -> 47 / 59 us; N = 192 FP32, 2 signals
-// 278 / 280 -> 62 / 74 us; N = 216 FP64, 2 signals 799 / 968 -> 264 / 228 us.
+// What bounds it: HBM in principle, and the traffic is N^2 + P values per ring
+// (counters: 1.01 times that at N = 54, 1.08 at N = 72, 1.00 at N = 192, whose
+// slices read their ring again from L2).  Full batches take 1.0-1.5 times as long
+// as a copy of those bytes at N = 24 to 48 and 1.5-1.7 at N = 54 to 96 (vector
+// ALUs 58 % busy at N = 72); N = 192 and 216 take 2.3-2.9 times, one workgroup
+// per CU, nothing covering its loads, steps and stores.  Ring stage alone, forward /
+// inverse, against one-radix-per-pass kernels with run-time sizes before: N = 54
+// FP64, 106 signals 291 / 293 -> 105 / 99 us; N = 72 FP32, 44 signals 140 / 142 ->
+// 49 / 54 us; N = 96 FP32, 18 signals 93 / 83 -> 48 / 53 us; N = 192 FP32, 2 signals
+// 278 / 280 -> 63 / 74 us; N = 216 FP64, 2 signals 799 / 968 -> 234 / 228 us.
 #include <algorithm>
 
 #include "su2fft_fused.h"
